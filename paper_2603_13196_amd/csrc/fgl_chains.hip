@@ -22,6 +22,9 @@
 // reads the chains' stages after each replay and stops when every chain is
 // done.
 //
+// Small models (the thin form) leave that scheme: k_chain_run keeps a chain in
+// one workgroup for all its rounds, so a round costs no launch.
+//
 // Coordinates: the sampler works in z = [beta.., A, nu21, w, log sigma] (or
 // [beta.., log sigma] without the 21-cm term), uniform over the box; the
 // likelihood row is z with its last entry exponentiated.
@@ -34,6 +37,7 @@
 // Box-Muller transform.
 #include "fgl_host.h"
 #include "fgl_philox.h"
+#include "fgl_pow2.h"
 
 #include <algorithm>
 #include <cmath>
@@ -60,6 +64,7 @@ struct ChainState {
   int* done;        // [n] finished steps
   int* expand;      // [n] expansions of the current side
   int* evals;       // [n] in-box proposals evaluated
+  long long* rounds;   // [n] rounds taken (k_chain_run)
   unsigned long long* ctr;   // [n] Philox counter
   double* theta;    // [n][P] likelihood rows of the proposals
   int* inbox;       // [n]
@@ -83,7 +88,7 @@ struct ChainState {
 
 // Two uniforms in [0, 1) with 53 random bits each, from Philox block c of
 // chain i.
-__device__ inline void uniform2(const ChainState& s, int i, unsigned long long c, double& u0,
+__device__ __forceinline__ void uniform2(const ChainState& s, int i, unsigned long long c, double& u0,
                                 double& u1) {
   uint32_t v[4] = {(uint32_t)c, (uint32_t)(c >> 32), (uint32_t)i, 0x5eed5eedu};
   philox4x32(v, (uint32_t)s.seed, (uint32_t)(s.seed >> 32));
@@ -128,12 +133,40 @@ __device__ inline void store_scal(const ChainState& s, int i, const Scal& c, int
   s.ctr[i] = c.ctr;
 }
 
+// A chain's coordinates: the lane holds entries lane + 64 q, q < Q, of the
+// point and of the step's direction.
+template <int Q>
+struct Coord {
+  double x[Q], d[Q];
+};
+constexpr int kQ = 3;
+static_assert(kMaxP <= kQ * 64, "three entries per lane");
+
+template <int Q>
+__device__ inline void load_coord(Coord<Q>& v, const double* x, const double* d, int P, int lane) {
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int k = lane + 64 * q;
+    v.x[q] = k < P ? x[k] : 0.0;
+    v.d[q] = k < P && d ? d[k] : 0.0;
+  }
+}
+
+template <int Q>
+__device__ inline void store_coord(const double (&v)[Q], double* to, int P, int lane) {
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (lane + 64 * q < P) to[lane + 64 * q] = v[q];
+}
+
 // A new slice step: direction uniform on the unit sphere in whitened
 // coordinates, mapped by the Cholesky factor; unit interval at a random
 // offset around the current point.  Lane k/2 draws the normal pair of
-// coordinates k, k + 1 (Philox block ctr + k/2); the pairs go through LDS
+// coordinates k, k + 1 (Philox block ctr + k/2); the pairs go through LDS (u)
 // so that lane j can form row j of the Cholesky product.
-__device__ void new_step(const ChainState& s, int i, Scal& c, int lane, double* u) {
+template <int Q>
+__device__ __forceinline__ void new_step(const ChainState& s, int i, Scal& c, int lane, double* u,
+                                         Coord<Q>& v) {
   const int P = s.P, np = (P + 1) / 2;
   double nrm = 0.0;
   // the direction needs randomness, not precision: the Box-Muller pairs are
@@ -141,8 +174,8 @@ __device__ void new_step(const ChainState& s, int i, Scal& c, int lane, double* 
   for (int pr = lane; pr < np; pr += 64) {
     double u0, u1;
     uniform2(s, i, c.ctr + pr, u0, u1);
-    const float v = (float)(1.0 - u0);                  // in (0, 1]
-    const float rad = __builtin_sqrtf(-2.0f * __logf(v));
+    const float w = (float)(1.0 - u0);                  // in (0, 1]
+    const float rad = __builtin_sqrtf(-2.0f * __logf(w));
     const float ang = 6.2831853f * (float)u1;
     const double z0 = (double)(rad * __cosf(ang)), z1 = (double)(rad * __sinf(ang));
     u[2 * pr] = z0;
@@ -155,11 +188,13 @@ __device__ void new_step(const ChainState& s, int i, Scal& c, int lane, double* 
   nrm = wave_sum(nrm);
   __builtin_amdgcn_wave_barrier();                      // u written by all lanes
   const double inv = 1.0 / sqrt(nrm);
-  double* d = s.dir + (size_t)i * P;
-  for (int j = lane; j < P; j += 64) {                  // dir = L u, L lower triangular
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {                         // dir = L u, L lower triangular
+    const int j = lane + 64 * q;
+    if (j >= P) continue;
     double acc = 0.0;
     for (int k = 0; k <= j; ++k) acc += s.chol[(size_t)j * P + k] * u[k];
-    d[j] = acc * inv;
+    v.d[q] = acc * inv;
   }
   __builtin_amdgcn_wave_barrier();                      // u read by all lanes
   double r, unused;
@@ -167,8 +202,6 @@ __device__ void new_step(const ChainState& s, int i, Scal& c, int lane, double* 
   c.ctr += np + 1;
   c.a = -r;
   c.b = 1.0 - r;
-  c.stage = kLeft;
-  c.expand = 0;
 }
 
 // The row record and the transposed spectral indices (and log2 alpha) of
@@ -265,9 +298,8 @@ __device__ void prep_row(const ChainState& s, int i, int lane, const double (&v)
 // the box, else (and for a finished chain) the chain's point itself, whose
 // result is ignored.  The last coordinate is log sigma.  The row's record
 // and transposed indices are prepared here too.
-__device__ void propose(const ChainState& s, int i, Scal& c, int lane) {
+__device__ void propose(const ChainState& s, int i, Scal& c, int lane, const Coord<kQ>& y) {
   const int P = s.P;
-  const double* x = s.x + (size_t)i * P;
   double* th = s.theta + (size_t)i * P;
   double v[3] = {0.0, 0.0, 0.0};
   if (c.stage == kDone) {
@@ -275,7 +307,7 @@ __device__ void propose(const ChainState& s, int i, Scal& c, int lane) {
     for (int q = 0; q < 3; ++q) {
       const int k = lane + 64 * q;
       if (k < P) {
-        v[q] = k == P - 1 ? exp(x[k]) : x[k];
+        v[q] = k == P - 1 ? exp(y.x[q]) : y.x[q];
         th[k] = v[q];
       }
     }
@@ -293,10 +325,12 @@ __device__ void propose(const ChainState& s, int i, Scal& c, int lane) {
     t = c.stage == kLeft ? c.a : c.b;
   }
   c.t = t;
-  const double* d = s.dir + (size_t)i * P;
   int out = 0;
-  for (int k = lane; k < P; k += 64) {
-    const double p = x[k] + t * d[k];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int k = lane + 64 * q;
+    if (k >= P) continue;
+    const double p = y.x[q] + t * y.d[q];
     out |= !((p >= s.lo[k]) & (p <= s.hi[k]));
   }
   const bool in = __builtin_amdgcn_ballot_w64(out != 0) == 0;
@@ -304,7 +338,7 @@ __device__ void propose(const ChainState& s, int i, Scal& c, int lane) {
   for (int q = 0; q < 3; ++q) {
     const int k = lane + 64 * q;
     if (k < P) {
-      const double p = in ? x[k] + t * d[k] : x[k];
+      const double p = in ? y.x[q] + t * y.d[q] : y.x[q];
       v[q] = k == P - 1 ? exp(p) : p;
       th[k] = v[q];
     }
@@ -313,12 +347,39 @@ __device__ void propose(const ChainState& s, int i, Scal& c, int lane) {
   prep_row(s, i, lane, v);
 }
 
-__device__ inline void finish_step(const ChainState& s, int i, Scal& c, int lane, double* u) {
+template <int Q>
+__device__ __forceinline__ void finish_step(const ChainState& s, int i, Scal& c, int lane,
+                                            double* u, Coord<Q>& y) {
   c.done += 1;
-  if (c.done >= s.steps)
-    c.stage = kDone;
-  else
-    new_step(s, i, c, lane, u);
+  const bool end = c.done >= s.steps;
+  if (!end) new_step(s, i, c, lane, u, y);
+  c.stage = end ? kDone : kLeft;
+  c.expand = 0;
+}
+
+// One transition of the state machine after the last proposal, x + t d
+// (inside the box or not), evaluated to lp; true when it ends the step.
+template <int Q>
+__device__ __forceinline__ bool advance(Scal& c, double lp, bool in, double lstar, Coord<Q>& y) {
+  // NaN and -inf are outside (ballots keep the state's branches scalar, selects
+  // keep the state in registers)
+  const bool inside = in && __builtin_amdgcn_ballot_w64(lp > lstar) != 0;
+  const bool left = c.stage == kLeft, out = c.stage != kShrink;   // stepping out
+  const bool grow = out && inside && c.expand < kMaxExpand;
+  const bool take = !out && inside;                // shrinking: accepted
+  const bool cut = !out && !inside, below = c.t < 0.0;
+  c.evals = in ? c.evals + 1 : c.evals;
+  c.a = grow && left ? c.a - 1.0 : cut && below ? c.t : c.a;
+  c.b = grow && !left ? c.b + 1.0 : cut && !below ? c.t : c.b;
+  c.expand = grow ? c.expand + 1 : 0;
+  c.stage = out && !grow ? (left ? kRight : kShrink) : c.stage;
+  c.lx = take ? lp : c.lx;
+  if (take) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) y.x[q] = y.x[q] + c.t * y.d[q];   // the proposal, exactly
+  }
+  // an interval shrunk to nothing (a likelihood plateau at lnL*): keep the point
+  return take || (cut && __builtin_amdgcn_ballot_w64(c.b - c.a < 1e-12) != 0);
 }
 
 // The likelihood kernel's partial sums of row b, reduced as the library's
@@ -330,15 +391,19 @@ struct RowSums {
   double nFT, chi0;
 };
 
-__device__ inline double row_lnl(const RowSums& r, int b, int lane) {
-  double acc = 0.0;
-  if (lane < 16)
-    for (int c = lane; c < r.ngroup; c += 16) acc += r.partial[(size_t)c * r.Bpad + b];
+__device__ inline double sum16(double acc) {
   acc += __shfl_xor(acc, 8);
   acc += __shfl_xor(acc, 4);
   acc += __shfl_xor(acc, 2);
   acc += __shfl_xor(acc, 1);
-  acc = __shfl(acc, 0);
+  return __shfl(acc, 0);
+}
+
+__device__ inline double row_lnl(const RowSums& r, int b, int lane) {
+  double acc = 0.0;
+  if (lane < 16)
+    for (int c = lane; c < r.ngroup; c += 16) acc += r.partial[(size_t)c * r.Bpad + b];
+  acc = sum16(acc);
   const RowParams rp = r.rows[b];
   if (!rp.valid) return -INFINITY;
   const double s2 = rp.sigma * rp.sigma;
@@ -354,17 +419,17 @@ __global__ __launch_bounds__(64 * kWaves) void k_chain_start(ChainState s, const
   const int i = blockIdx.x * kWaves + wv;
   if (i >= s.n) return;
   const int P = s.P;
-  for (int k = lane; k < P; k += 64) s.x[(size_t)i * P + k] = x0[(size_t)i * P + k];
+  Coord<kQ> y;
+  load_coord(y, x0 + (size_t)i * P, nullptr, P, lane);
+  store_coord(y.x, s.x + (size_t)i * P, P, lane);
   Scal c = load_scal(s, i);             // ctr keeps counting across calls: fresh numbers
   c.lx = l0[i];
-  c.done = 0;
+  c.done = -1;                          // the first step starts as any other
   c.evals = 0;
   c.t = 0.0;
-  if (s.steps > 0)
-    new_step(s, i, c, lane, s_u[wv]);
-  else
-    c.stage = kDone;
-  propose(s, i, c, lane);
+  finish_step(s, i, c, lane, s_u[wv], y);
+  store_coord(y.d, s.dir + (size_t)i * P, P, lane);
+  propose(s, i, c, lane, y);
   store_scal(s, i, c, lane);
 }
 
@@ -380,37 +445,324 @@ __global__ __launch_bounds__(64 * kWaves) void k_chain_step(ChainState s, RowSum
   if (c.stage == kDone) return;
   const double lp = row_lnl(rs, i, lane);
   if (lane == 0) s.lnl[i] = lp;
-  const bool in = s.inbox[i] != 0;
-  if (in) c.evals += 1;
-  const bool inside = in && (lp > lstar);          // NaN and -inf are outside
-  if (c.stage == kLeft || c.stage == kRight) {
-    if (inside && c.expand < kMaxExpand) {
-      if (c.stage == kLeft)
-        c.a -= 1.0;
-      else
-        c.b += 1.0;
-      c.expand += 1;
-    } else {
-      c.stage = c.stage == kLeft ? kRight : kShrink;
-      c.expand = 0;
-    }
-  } else if (inside) {                             // shrinking: accepted
-    const int P = s.P;
-    double* x = s.x + (size_t)i * P;
-    const double* d = s.dir + (size_t)i * P;
-    for (int k = lane; k < P; k += 64) x[k] = x[k] + c.t * d[k];   // the proposal, exactly
-    c.lx = lp;
-    finish_step(s, i, c, lane, s_u[wv]);
-  } else {                                         // shrinking: cut the interval
-    if (c.t < 0.0)
-      c.a = c.t;
-    else
-      c.b = c.t;
-    // an interval shrunk to nothing (a likelihood plateau at lnL*): keep the point
-    if (c.b - c.a < 1e-12) finish_step(s, i, c, lane, s_u[wv]);
+  Coord<kQ> y;
+  load_coord(y, s.x + (size_t)i * s.P, s.dir + (size_t)i * s.P, s.P, lane);
+  if (advance(c, lp, s.inbox[i] != 0, lstar, y)) {
+    finish_step(s, i, c, lane, s_u[wv], y);
+    store_coord(y.x, s.x + (size_t)i * s.P, s.P, lane);
+    store_coord(y.d, s.dir + (size_t)i * s.P, s.P, lane);
   }
-  propose(s, i, c, lane);
+  propose(s, i, c, lane, y);
   store_scal(s, i, c, lane);
+}
+
+// ---------------------------------------------------------------------------
+// small models: a chain's rounds inside one workgroup
+//
+// A round of the launches above is two dependent kernels over a few dozen
+// rows, so a call of 70 chains (14 parameters, 70 steps, ~2200 rounds) is
+// launch latency: 12.5 us a round.  Chains never exchange anything, so here
+// one workgroup owns a chain and runs its rounds in a loop.  What bounds a
+// round is then the latency of its serial chain, and the waves split it:
+//   wave 0       the state machine (the code above), its coordinates in
+//                registers, and sigma = exp(log sigma) with ln(2 pi sigma^2)
+//                while the channels are evaluated;
+//   wave 1       the uniform a following shrink step would draw;
+//   waves 2 ..   one channel per lane of the thin kernel's model, the same
+//                operations in the same order, so lnL is bitwise what the
+//                library returns.
+// Proposals outside the box or invalid cost no evaluation.  Two barriers a
+// round; a launch ends after kRunRounds rounds (state saved) so that no
+// launch lasts long.
+
+constexpr int kRunRounds = 4096;        // rounds of one k_chain_run launch (5-10 ms)
+constexpr int kRunMaxThreads = 512;
+constexpr int kRunHelpers = 128;        // threads of waves 0 and 1
+constexpr int kRunMaxP = 64;            // one coordinate per lane (thin models have at most 37)
+
+// The thin model laid out for one lane per channel: K as [T][NT/4][Fp] quads
+// of regions and D as [T][Fp], Fp = F rounded up to 64.
+struct RunModel {
+  const float4* k;
+  const double* d;
+  int Fp;
+};
+
+// k and d of a RunModel from the thin kernel's K [F][T][NT] and D [F][TT 32].
+__global__ __launch_bounds__(256) void k_run_layout(DevModel m, int Fp, float4* __restrict__ k,
+                                                    double* __restrict__ d) {
+  const int f = blockIdx.x * blockDim.x + threadIdx.x, t = blockIdx.y, nq = m.NT / 4;
+  if (f >= Fp) return;
+  for (int q = 0; q < nq; ++q)
+    k[((size_t)t * nq + q) * Fp + f] =
+        f < m.F ? reinterpret_cast<const float4*>(m.kthin)[((size_t)f * m.T + t) * nq + q]
+                : make_float4(0.f, 0.f, 0.f, 0.f);
+  d[(size_t)t * Fp + f] = f < m.F ? m.D[(size_t)f * m.TT * 32 + t] : 0.0;
+}
+
+// Partials per row, padded so that sixteen lanes read four each at a time.
+__host__ __device__ inline int run_parts(int F) { return ((F + 3) / 4 + 63) / 64 * 64; }
+
+// dynamic LDS of k_chain_run: the partials, residuals [T][E]
+inline size_t run_lds(int T, int E, int F) {
+  return ((size_t)T * E + run_parts(F)) * sizeof(double);
+}
+
+// v of the lane `by` above, within rows of sixteen lanes (0 past the row)
+template <int by>
+__device__ inline double row_down(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x100 | by, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x100 | by, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// v of one lane (the same in every lane's call)
+__device__ inline double any_lane(double v, int of) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, of);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), of);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// ONE: one time bin and a lane for every channel, whose constants then stay in
+// registers over the rounds.
+template <int NT, bool AB, bool ONE>
+__global__ __launch_bounds__(kRunMaxThreads) void k_chain_run(ChainState s, DevModel m,
+                                                              RunModel rm, double nFT, int first,
+                                                              const double* __restrict__ x0,
+                                                              const double* __restrict__ l0,
+                                                              long long limit) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double s_u[64], s_v[64], s_t64[64];
+  __shared__ double s_unif;
+  __shared__ unsigned long long s_ctr;
+  __shared__ int s_go;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, E = blockDim.x - kRunHelpers;
+  const int i = blockIdx.x, P = s.P, F = m.F, T = m.T;
+  const int nparts = run_parts(F);
+  double* s_part = reinterpret_cast<double*>(smem);
+  double* s_r = s_part + nparts;                    // [T][E]
+  const bool no21 = s.flags & 1u;
+  init_t64(s_t64);
+  for (int k = tid; k < nparts; k += blockDim.x) s_part[k] = 0.0;
+
+  if (wave == 0) {
+    const double lstar = *s.lstar;
+    const double lo = lane < P ? s.lo[lane] : -1.0, hi = lane < P ? s.hi[lane] : 1.0;
+    const bool is_beta = lane < s.NB, is_alpha = !is_beta && lane < s.NB + s.NA;
+    const bool is_width = !no21 && lane == P - 2;
+    Coord<1> y;
+    Scal c = load_scal(s, i);
+    long long rounds = 0;
+    bool over = first != 0;                         // a step is to begin
+    if (first) {
+      load_coord(y, x0 + (size_t)i * P, nullptr, P, lane);
+      c.lx = l0[i];
+      c.done = -1;                                  // the first step starts as any other
+      c.evals = 0;
+      c.t = 0.0;
+    } else {
+      load_coord(y, s.x + (size_t)i * P, s.dir + (size_t)i * P, P, lane);
+      rounds = s.rounds[i];
+    }
+    unsigned long long drawn = ~0ull;               // counter whose uniform wave 1 formed
+    double lp = -INFINITY;
+    bool in = false, made = false;                  // made: a proposal has its lp
+    for (;;) {
+      if (made) {
+        over = advance(c, lp, in, lstar, y);
+        ++rounds;
+      }
+      if (over) finish_step(s, i, c, lane, s_u, y);
+      over = false;
+      if (c.stage == kDone || rounds >= limit) break;
+      made = true;
+      // the next proposal's position, as propose() draws it
+      if (c.stage == kShrink) {
+        double u = s_unif, unused;
+        if (drawn != c.ctr) uniform2(s, i, c.ctr, u, unused);
+        c.ctr += 1;
+        c.t = c.a + (c.b - c.a) * u;
+      } else {
+        c.t = c.stage == kLeft ? c.a : c.b;
+      }
+      // its row, but for sigma, into LDS (entries past P are 0, inside their
+      // box of -1 .. 1; inside the box entries are finite)
+      const double p = y.x[0] + c.t * y.d[0];
+      const bool out = !((p >= lo) & (p <= hi));
+      const bool bad = (is_beta & !(fabs(p) <= 64.0)) | (is_width & !(p > 0.0)) |
+                       (is_alpha & !(p >= 0x1p-32 && p <= 0x1p32));
+      // amplitude scales as the exponents they add: 64 log2 alpha
+      if (lane < P) s_v[lane] = AB && is_alpha ? 64.0 * log2(p) : p;
+      in = __builtin_amdgcn_ballot_w64(out) == 0;
+      lp = -INFINITY;
+      if (!in || __builtin_amdgcn_ballot_w64(bad) != 0) continue;   // nothing to evaluate
+      const double last = any_lane(p, P - 1);
+      drawn = c.ctr;
+      if (lane == 0) {
+        s_ctr = drawn;
+        s_go = 1;
+      }
+      __syncthreads();
+      const double sigma = exp(last), s2 = sigma * sigma;
+      const double ln = log(2.0 * M_PI * s2);
+      __syncthreads();
+      double acc = 0.0;
+      for (int g = 0; g < nparts; g += 64) {        // group order within a sum; padding is 0
+        const double* at = s_part + g + (lane & 15);
+        const double v0 = at[0], v1 = at[16], v2 = at[32], v3 = at[48];
+        acc += v0;
+        acc += v1;
+        acc += v2;
+        acc += v3;
+      }
+      acc += row_down<8>(acc);
+      acc += row_down<4>(acc);
+      acc += row_down<2>(acc);
+      acc += row_down<1>(acc);
+      acc = any_lane(acc, 0);
+      if (isfinite(sigma) && sigma > 0.0) lp = -0.5 * (acc + 0.0) / s2 - 0.5 * nFT * ln;
+    }
+    if (lane == 0) s_go = 0;
+    __syncthreads();
+    store_coord(y.x, s.x + (size_t)i * P, P, lane);
+    store_coord(y.d, s.dir + (size_t)i * P, P, lane);
+    store_scal(s, i, c, lane);
+    if (lane == 0) s.rounds[i] = rounds;
+    return;
+  }
+
+  if (wave == 1) {
+    for (;;) {
+      __syncthreads();
+      if (!s_go) return;
+      double u, unused;
+      uniform2(s, i, s_ctr, u, unused);
+      s_unif = u;
+      __syncthreads();
+    }
+  }
+
+  const int id = tid - kRunHelpers;                 // channel f0 + id of every pass
+  const int own = min(id, F - 1);
+  const double nl0 = m.nl64[own], nu0 = m.nu[own], d0 = rm.d[own];
+  float k0[NT];
+  if constexpr (ONE) {
+#pragma unroll
+    for (int q = 0; q < NT / 4; ++q) {
+      const float4 k = rm.k[(size_t)q * rm.Fp + own];
+      k0[4 * q] = k.x;
+      k0[4 * q + 1] = k.y;
+      k0[4 * q + 2] = k.z;
+      k0[4 * q + 3] = k.w;
+    }
+  }
+  for (;;) {
+    __syncthreads();
+    if (!s_go) return;
+    const double A = no21 ? 0.0 : s_v[P - 4], c21 = no21 ? 0.0 : s_v[P - 3];
+    const double inv_w = no21 ? 1.0 : 1.0 / s_v[P - 2];
+    for (int f0 = 0; f0 < F; f0 += E) {
+      const int f = f0 + id;
+      if (f < F) {
+        const double nl = ONE ? nl0 : m.nl64[f];
+        const double z = ((ONE ? nu0 : m.nu[f]) - c21) * inv_w;
+        const double cc = m.t_cmb + A * exp(-0.5 * z * z);
+        double Pw[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          // regions past N have K = 0: any finite power will do
+          const int jr = min(j, s.N - 1), ia = AB ? jr / s.NB : 0, jb = AB ? jr - ia * s.NB : jr;
+          const double b = s_v[jb];
+          Pw[j] = pow2_64(AB ? fma(b, nl, s_v[s.NB + ia]) : b * nl, s_t64, m);
+        }
+        if constexpr (ONE) {
+          double msum = 0.0;
+#pragma unroll
+          for (int j = 0; j < NT; ++j) msum = fma((double)k0[j], Pw[j], msum);
+          s_r[id] = (d0 - cc) - msum;
+        } else {
+          // U bins at a time, so that their loads and chains overlap
+          constexpr int U = NT <= 8 ? 8 : NT <= 12 ? 4 : 2;
+          for (int t0 = 0; t0 < T; t0 += U) {
+            float4 k[U][NT / 4];
+            double dv[U], ms[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const size_t t = min(t0 + u, T - 1);
+#pragma unroll
+              for (int q = 0; q < NT / 4; ++q) k[u][q] = rm.k[(t * (NT / 4) + q) * rm.Fp + f];
+              dv[u] = rm.d[t * rm.Fp + f];
+              ms[u] = 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < NT / 4; ++q)
+#pragma unroll
+              for (int u = 0; u < U; ++u) {
+                ms[u] = fma((double)k[u][q].x, Pw[4 * q], ms[u]);
+                ms[u] = fma((double)k[u][q].y, Pw[4 * q + 1], ms[u]);
+                ms[u] = fma((double)k[u][q].z, Pw[4 * q + 2], ms[u]);
+                ms[u] = fma((double)k[u][q].w, Pw[4 * q + 3], ms[u]);
+              }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (t0 + u < T) s_r[(size_t)(t0 + u) * E + id] = (dv[u] - cc) - ms[u];
+          }
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();              // a group's four lanes are in one wave
+      if (f < F && (id & 3) == 0) {
+        // channels in order, time bins in order: one chain of fmas, its
+        // residuals read eight ahead
+        double acc = 0.0;
+        const int nq = min(4, F - f);
+        if constexpr (ONE) {
+          for (int q = 0; q < nq; ++q) acc = fma(s_r[id + q], s_r[id + q], acc);
+        } else {
+          for (int q = 0; q < nq; ++q) {
+            const double* r = s_r + id + q;
+            int t = 0;
+            for (; t + 8 <= T; t += 8) {
+              double v[8];
+#pragma unroll
+              for (int u = 0; u < 8; ++u) v[u] = r[(size_t)(t + u) * E];
+#pragma unroll
+              for (int u = 0; u < 8; ++u) acc = fma(v[u], v[u], acc);
+            }
+            for (; t < T; ++t) acc = fma(r[(size_t)t * E], r[(size_t)t * E], acc);
+          }
+        }
+        s_part[f >> 2] = acc;
+      }
+      __builtin_amdgcn_wave_barrier();              // s_r is free for the next channels
+    }
+    __syncthreads();
+  }
+}
+
+using RunKernel = void (*)(ChainState, DevModel, RunModel, double, int, const double*,
+                           const double*, long long);
+
+template <bool AB, bool ONE>
+RunKernel run_kernel(int NT) {
+  switch (NT) {
+    case 4: return k_chain_run<4, AB, ONE>;
+    case 8: return k_chain_run<8, AB, ONE>;
+    case 12: return k_chain_run<12, AB, ONE>;
+    case 16: return k_chain_run<16, AB, ONE>;
+    case 24: return k_chain_run<24, AB, ONE>;
+    case 32: return k_chain_run<32, AB, ONE>;
+    default: return nullptr;
+  }
+}
+
+// Evaluation lanes of k_chain_run: a lane per channel (a channel loop past
+// 384), with the residuals of all lanes within 96 KB of LDS (T <= 64).
+int run_lanes(const DevModel& m) {
+  const int most = 96 * 1024 / (8 * m.T) / 64 * 64;
+  return std::min({(m.F + 63) / 64 * 64, kRunMaxThreads - kRunHelpers, most});
 }
 
 }  // namespace
@@ -425,6 +777,8 @@ struct Chains {
   double *d_x0 = nullptr, *d_l0 = nullptr, *d_chol = nullptr, *d_lo = nullptr, *d_hi = nullptr;
   double* d_lstar = nullptr;
   int* h_stage = nullptr;                       // pinned
+  float4* d_rk = nullptr;                       // the model laid out for k_chain_run
+  double* d_rd = nullptr;
   std::vector<double> lo, hi;
   unsigned long long seed = 0;
   unsigned long long calls = 0;
@@ -441,7 +795,8 @@ struct Chains {
 static void chains_free(Chains* c) {
   void* ps[] = {c->st.x, c->st.dir, c->st.a, c->st.b, c->st.t, c->st.lx, c->st.stage,
                 c->st.done, c->st.expand, c->st.evals, c->st.ctr, c->st.theta, c->st.inbox,
-                c->st.lnl, c->d_x0, c->d_l0, c->d_chol, c->d_lo, c->d_hi, c->d_lstar};
+                c->st.lnl, c->st.rounds, c->d_x0, c->d_l0, c->d_chol, c->d_lo, c->d_hi, c->d_lstar,
+                c->d_rk, c->d_rd};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   if (c->h_stage) (void)hipHostFree(c->h_stage);
@@ -466,6 +821,99 @@ __global__ void k_philox(const uint32_t* __restrict__ ctr, int n, uint32_t k0, u
 }
 
 constexpr int kPhiloxMaxBlocks = 1 << 24;
+
+// Whether a call's rounds run in place (k_chain_run): the model's thin form
+// for this precision, no kernel timing (whose events bracket the likelihood
+// kernel of the launched rounds), and few enough chains.  A launched round costs
+// 11-13 us plus the batch's throughput; a round in place costs its latency
+// (passes over the channels, each with a serial chain over the time bins), once
+// per generation of resident workgroups.  Both measured per call (ms, launched
+// and in place; one card, 301 channels but for N10's 151):
+//   N10 T1  n 70: 28.1, 3.9    n 1000: 11.1, 3.3    n 4000: 10.0, 5.4
+//   N16 T20 n 100: 22.4, 6.4   n 1000: 28.0, 15.1   n 4000: 32.0, 26.7-43
+//   N8 T40  n 100: 17.4, 9.5   n 1000: 21.8, 32.0   N4 T64 n 400: 12.1, 16.4
+// so the line lies at 96 channel passes x bins (at least 8) x generations.
+constexpr int kRunCost = 96;
+static bool run_takes(const Model* m, int prec, int n) {
+  const DevModel& d = m->dm;
+  if (kind_of(prec, d) != kThin || group_of(kThin, d) != 4 || m->timing || m->P > kRunMaxP ||
+      run_parts(d.F) > 2048)
+    return false;
+  const int E = run_lanes(d), passes = (d.F + E - 1) / E;
+  const int by_lds = (int)(max_lds_bytes() / (run_lds(d.T, E, d.F) + 2048));
+  const int per_cu = std::max(1, std::min(by_lds, 16 / (E / 64 + 2)));
+  const int64_t gens = ((int64_t)n + kCUs * per_cu - 1) / (kCUs * per_cu);
+  return gens * passes * std::max(d.T, 8) <= kRunCost;
+}
+
+// The call's rounds by k_chain_run, from the inputs already queued on the
+// engine's stream.  The counts reported are those of the launched rounds: one,
+// then batches of kRoundsPerGraph until every chain is done.
+static int run_in_place(Chains* c, ChainState st, long long max_rounds, double* x_out,
+                        double* l_out, int64_t* evals, int64_t* rounds) {
+  Model* m = c->m;
+  const DevModel& d = m->dm;
+  hipStream_t s = c->s;
+  const int n = st.n, P = c->P, Fp = (d.F + 63) / 64 * 64;
+  hipError_t e = hipSuccess;
+  if (!c->d_rd) {
+    if ((e = dalloc(&c->d_rk, (size_t)d.T * (d.NT / 4) * Fp)) == hipSuccess &&
+        (e = dalloc(&c->d_rd, (size_t)d.T * Fp)) == hipSuccess) {
+      hipLaunchKernelGGL(k_run_layout, dim3((Fp + 255) / 256, d.T), dim3(256), 0, s, d, Fp,
+                         c->d_rk, c->d_rd);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) {
+      (void)hipStreamSynchronize(s);
+      if (c->d_rk) (void)hipFree(c->d_rk);
+      if (c->d_rd) (void)hipFree(c->d_rd);
+      c->d_rk = nullptr;
+      c->d_rd = nullptr;
+      return hip_err(e, "laying out the model for the chains");
+    }
+  }
+  const int E = run_lanes(d);
+  const bool one = d.T == 1 && d.F <= E;
+  const RunKernel kern = d.NA > 0 ? (one ? run_kernel<true, true>(d.NT) : run_kernel<true, false>(d.NT))
+                                  : (one ? run_kernel<false, true>(d.NT) : run_kernel<false, false>(d.NT));
+  if (!kern) return set_err(FGL_EINVAL, "NT=%d has no chain kernel", d.NT);
+  const size_t lds = run_lds(d.T, E, d.F);
+  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 120 * 1024)) != hipSuccess)
+    return hip_err(e, "chain kernel LDS");
+  const long long cap = 1 + (max_rounds - 1 + kRoundsPerGraph - 1) / kRoundsPerGraph * kRoundsPerGraph;
+  std::vector<int> ev(n);
+  std::vector<long long> nr(n);
+  bool all = false;
+  long long limit = 0;
+  for (int first = 1; !all && limit < cap; first = 0) {
+    limit = std::min<long long>(cap, limit + kRunRounds);
+    hipLaunchKernelGGL(kern, dim3(n), dim3(E + kRunHelpers), lds, s, st, d, RunModel{c->d_rk, c->d_rd, Fp},
+                       (double)d.F * (double)d.T, first, c->d_x0, c->d_l0, limit);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_err(e, "chain rounds");
+    if ((e = hipMemcpyAsync(c->h_stage, st.stage, (size_t)n * sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipMemcpyAsync(x_out, st.x, (size_t)n * P * 8, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipMemcpyAsync(l_out, st.lx, (size_t)n * 8, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipMemcpyAsync(ev.data(), st.evals, (size_t)n * sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipMemcpyAsync(nr.data(), st.rounds, (size_t)n * sizeof(long long), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipStreamSynchronize(s)) != hipSuccess)
+      return hip_err(e, "copy chain results");
+    all = true;
+    for (int i = 0; i < n && all; ++i) all = c->h_stage[i] == kDone;
+  }
+  if (!all) return set_err(FGL_EAGAIN, "chains did not finish within %lld rounds", max_rounds);
+  if (evals) {
+    int64_t sum = 0;
+    for (int v : ev) sum += v;
+    *evals = sum;
+  }
+  if (rounds) {
+    const int64_t most = (int64_t)*std::max_element(nr.begin(), nr.end());
+    *rounds = 1 + std::max<int64_t>(1, (most - 1 + kRoundsPerGraph - 1) / kRoundsPerGraph) * kRoundsPerGraph;
+  }
+  c->calls++;
+  return FGL_OK;
+}
 
 }  // namespace fgl
 
@@ -508,6 +956,7 @@ int fgl_chains_create(fgl_model* mh, int max_chains, const double* lo, const dou
   if (e == hipSuccess) e = dalloc(&s.done, n);
   if (e == hipSuccess) e = dalloc(&s.expand, n);
   if (e == hipSuccess) e = dalloc(&s.evals, n);
+  if (e == hipSuccess) e = dalloc(&s.rounds, n);
   if (e == hipSuccess) e = dalloc(&s.ctr, n);
   if (e == hipSuccess) e = dalloc(&s.theta, n * P);
   if (e == hipSuccess) e = dalloc(&s.inbox, n);
@@ -575,6 +1024,14 @@ int fgl_chains_run(fgl_chains* ch, const double* x0, const double* l0, int n, do
       (e = hipMemcpyAsync(c->d_lstar, &lstar, 8, hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_err(e, "copy chain inputs");
   if (P > kMaxP) return set_err(FGL_EINVAL, "P=%d exceeds the chains' %d parameters", P, kMaxP);
+  st.N = m->dm.N;
+  st.NA = m->dm.NA;
+  st.NB = m->dm.NB;
+  st.betaRows = m->dm.KC * 32;
+  st.flags = m->dm.flags;
+  // the bound covers steps of at most 2 kMaxExpand + 64 rounds each
+  const long long max_rounds = (long long)std::max(steps, 1) * (2 * kMaxExpand + 66);
+  if (run_takes(m, prec, n)) return run_in_place(c, st, max_rounds, x_out, l_out, evals, rounds);
   const int blocks = (n + kWaves - 1) / kWaves;
   // the likelihood's workspace for n rows on this stream, fixed before the
   // start kernel (which writes the first proposals' row records into it)
@@ -588,11 +1045,6 @@ int fgl_chains_run(fgl_chains* ch, const double* x0, const double* l0, int n, do
   st.betaT = wb.w.betaT;
   st.offT = wb.w.offT;
   st.Bpad = wb.w.Bpad;
-  st.N = m->dm.N;
-  st.NA = m->dm.NA;
-  st.NB = m->dm.NB;
-  st.betaRows = m->dm.KC * 32;
-  st.flags = m->dm.flags;
   hipLaunchKernelGGL(k_chain_start, dim3(blocks), dim3(64 * kWaves), 0, s, st, c->d_x0, c->d_l0);
   if ((e = hipGetLastError()) != hipSuccess) return hip_err(e, "chain start");
   // the padding rows up to Bpad (and the first proposals again, with the
@@ -648,9 +1100,7 @@ int fgl_chains_run(fgl_chains* ch, const double* x0, const double* l0, int n, do
     c->g_work = wb.w.partial;
     c->g_tile = tile;
   }
-  // replay until every chain is done; the bound covers steps of at most
-  // 2 kMaxExpand + 64 rounds each
-  const long long max_rounds = (long long)std::max(steps, 1) * (2 * kMaxExpand + 66);
+  // replay until every chain is done
   while (done_rounds < max_rounds) {
     if (c->graph) {
       if ((e = hipGraphLaunch(c->graph, s)) != hipSuccess) return hip_err(e, "graph launch");
