@@ -13,6 +13,9 @@
 //   I(q)      = sum_{nu, t} omega a(q, nu) b(nu, p_t(q)) / Z(nu, t)
 //   K_j(nu, t) = sum_{q in region j} omega t_ex(q) D(nu, p_t(q))
 // with a = T_sky (Eq. skyapproximation) or 1 and b = D H or H by scheme.
+// Z and I of steps on a regular grid of lags (evenly spaced steps) are the
+// Toeplitz kernels k_lag_corr and k_lag_imp; scattered steps take k_sky_corr and
+// k_sky_importance.
 // k_sky_corr computes Z: one workgroup per (block of four channels, chunk of
 // four rings), two lanes per time step, the ring's b window and weights
 // staged in LDS.  k_sky_k
@@ -51,15 +54,24 @@ struct SkyDev {
                          // pixel side by side (zero past the last channel)
 };
 
+int pad_to(int n, int m) { return (n + m - 1) / m * m; }
+int pad8(int n) { return pad_to(n, 8); }
+int pad4(int n) { return pad_to(n, 4); }
+
 enum Corr { kCorrBeam = 1, kCorrSky = 2, kCorrHorizon = 3 };
 
-// weight a(q, nu) of a sky pixel, omega included
+// weight a(q, nu) of a sky pixel, omega included, from its t_ex and beta
+template <int MODE>
+__device__ inline double aval_of(const SkyDev& s, int f, double omega, double t_ex, double beta) {
+  if constexpr (MODE == kCorrHorizon) return omega;
+  // Eq. skyapproximation
+  return omega * fma(t_ex, exp2(-beta * s.lr[f]), s.t_cmb);
+}
 template <int MODE>
 __device__ inline double aval(const SkyDev& s, int f, int ring, int ra) {
   const size_t px = (size_t)ring * s.nlon + ra;
-  if constexpr (MODE == kCorrHorizon) return s.omega[ring];
-  // Eq. skyapproximation
-  return s.omega[ring] * fma(s.t_ex[px], exp2(-s.beta[px] * s.lr[f]), s.t_cmb);
+  return aval_of<MODE>(s, f, s.omega[ring], MODE == kCorrHorizon ? 0.0 : s.t_ex[px],
+                       MODE == kCorrHorizon ? 0.0 : s.beta[px]);
 }
 
 // b(nu, ring, ha) of the four channels 4 fb .. 4 fb + 3 for a weighting (zero
@@ -444,15 +456,369 @@ __global__ __launch_bounds__(256) void k_sky_importance(SkyDev s, const int* __r
   }
 }
 
+// ---------------------------------------------------------------------------
+// normalisers and importance on a lag grid
+//
+// When the steps' shifts are multiples of g up to g (S - 1) with S not far from
+// the number of steps (evenly spaced steps), Z and I are Toeplitz products on
+// the columns of a residue class mod g: Z at lag s sums b[h] a[h + s], and
+// I sums b[q - s] / Z_s over s.  A lane takes 16 x 16 blocks of such a product
+// with the 31 diagonal values in registers, so an LDS value feeds about ten
+// fmas (the gathers of the kernels above feed one each, and pay an FP32
+// convert per fma).  Blocks of columns below the horizon, where b is zero, are
+// left out (about half of a sky).  All S lags are summed; a step's Z is the one
+// of its lag.  On the 256 x 512 sky, 301 channels and 96 steps, beam weighting:
+// Z 486 -> 188 us, I 426 -> 226 us (kernel trace).  What is left is vector
+// issue: the fmas of the blocks (about 55 us at the FP64 peak each), the FP64
+// powers of the staged weights (a quarter of the instructions), and the staging
+// loads that three waves per SIMD do not hide.
+
+// Columns h = c + g i of class c and index i sit in blocks of 16 indices: HB
+// blocks per class hold the nlon columns, and SB blocks hold the S lags.  The
+// arrays indexed by h + lag (or q - lag) have HB + SB blocks per class, each
+// padded to 17 entries so that lanes a block apart meet different LDS banks.
+struct Lag {
+  int g, S, SB, HB, smax;
+  unsigned inv_g;        // ceil(2^32 / g): e / g = umulhi(e, inv_g) for e g < 2^32 (g > 1)
+  __host__ __device__ int blocks() const { return g * HB; }
+  __host__ __device__ int ext() const { return g * (HB + SB); }
+};
+constexpr int kLagBlock = 16, kLagPad = 17;
+
+__device__ inline int lag_class(const Lag& p, int e, int& idx) {
+  idx = p.g == 1 ? e : (int)__umulhi((unsigned)e, p.inv_g);
+  return e - idx * p.g;
+}
+
+// Per ring, the blocks of b that hold a column above the horizon (as the
+// padded start of their block in the h + lag array, and their start in b) and
+// the tasks of the importance kernel: (column block, lag block) pairs that can
+// see one of them, in column-block order, and where each column block's begin.
+// One wave per ring.
+__global__ __launch_bounds__(64) void k_lag_blocks(SkyDev s, Lag p, int2* __restrict__ blist,
+                                                   int* __restrict__ bcount,
+                                                   int2* __restrict__ tasks,
+                                                   int* __restrict__ tstart) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int ring = blockIdx.x, lane = threadIdx.x;
+  const int NBk = p.blocks(), NE = p.ext(), NT = NBk * p.SB, off = p.SB * kLagBlock;
+  unsigned char* s_b = smem;                         // [NBk]
+  unsigned char* s_e = smem + NBk;                   // [NE] blocks of the q - lag array
+  for (int k = lane; k < NBk + NE; k += 64) smem[k] = 0;
+  __syncthreads();
+  for (int q = lane; q < s.nlon; q += 64) {
+    if (!s.hor[(size_t)ring * s.nlon + q]) continue;
+    int i;
+    const int c = lag_class(p, q, i);
+    s_b[c * p.HB + i / kLagBlock] = 1;
+    // column q at q itself and, wrapped, at q - nlon (entry e holds column
+    // e - g off)
+    s_e[c * (p.HB + p.SB) + (i + off) / kLagBlock] = 1;
+    if (q - s.nlon >= -p.smax) {
+      int iw;
+      const int cw = lag_class(p, q - s.nlon + p.g * off, iw);
+      s_e[cw * (p.HB + p.SB) + iw / kLagBlock] = 1;
+    }
+  }
+  __syncthreads();
+  int n = 0;
+  for (int k0 = 0; k0 < NBk; k0 += 64) {
+    const int k = k0 + lane, c = k / p.HB;
+    const bool on = k < NBk && s_b[k];
+    const unsigned long long m = __ballot(on);
+    if (on)
+      blist[(size_t)ring * NBk + n + __popcll(m & ((1ull << lane) - 1))] =
+          make_int2((c * (p.HB + p.SB) + k - c * p.HB) * kLagPad, k * kLagBlock);
+    n += __popcll(m);
+  }
+  if (lane == 0) bcount[ring] = n;
+  n = 0;
+  for (int k0 = 0; k0 < NT; k0 += 64) {
+    const int k = k0 + lane, blk = k / p.SB, sb = k - blk * p.SB, c = blk / p.HB;
+    // q - lag spans the last 15 entries of one block and the next block
+    const int m0 = c * (p.HB + p.SB) + (blk - c * p.HB) - sb + p.SB - 1;
+    const bool on = k < NT && (s_e[k < NT ? m0 : 0] | s_e[k < NT ? m0 + 1 : 0]);
+    const unsigned long long m = __ballot(on);
+    const int at = n + __popcll(m & ((1ull << lane) - 1));
+    if (k < NT && sb == 0) tstart[(size_t)ring * (NBk + 1) + blk] = at;
+    if (on) tasks[(size_t)ring * NT + at] = make_int2(m0 * kLagPad, blk | sb << 20);
+    n += __popcll(m);
+  }
+  if (lane == 0) tstart[(size_t)ring * (NBk + 1) + NBk] = n;
+}
+
+// What staging a column of a ring takes from memory.
+struct LagCol {
+  float4 b;              // the four channels' b
+  double t_ex, beta;
+};
+template <int MODE>
+__device__ inline LagCol lag_col(const SkyDev& s, int fb, int ring, int q) {
+  const size_t px = (size_t)ring * s.nlon + q;
+  const bool up = s.hor[px] != 0;                    // no load waits for another
+  float4 b = make_float4(1.f, 1.f, 1.f, 1.f);
+  if constexpr (MODE == kCorrBeam) b = s.beam4[((size_t)fb * s.nlat) * s.nlon + px];
+  LagCol v;
+  v.b = make_float4(up ? b.x : 0.f, up ? b.y : 0.f, up ? b.z : 0.f, up ? b.w : 0.f);
+  v.t_ex = MODE == kCorrHorizon ? 0.0 : s.t_ex[px];
+  v.beta = MODE == kCorrHorizon ? 0.0 : s.beta[px];
+  return v;
+}
+
+// partial[(chunk F + f) 16 SB + lag] = sum over the chunk's rings of
+// b[h] a[h + lag]: four channels per workgroup, one per wave.  A wave's lanes
+// are lag blocks x groups of column blocks; the groups' sums meet in LDS.
+template <int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_lag_corr(SkyDev s, Lag p, const int2* __restrict__ blist,
+                                                  const int* __restrict__ bcount, int rings,
+                                                  double* __restrict__ partial) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int fb = blockIdx.x, chunk = blockIdx.y, nlon = s.nlon;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int NBk = p.blocks(), NA = p.ext() * kLagPad, NB16 = NBk * kLagBlock;
+  double* s_a = reinterpret_cast<double*>(smem);                    // [4][NA]
+  float* s_b = reinterpret_cast<float*>(s_a + 4 * (size_t)NA);      // [4][NB16]
+  int2* s_l = reinterpret_cast<int2*>(s_b + 4 * (size_t)NB16);      // [NBk]
+  for (int k = tid; k < 4 * NA; k += 256) s_a[k] = 0.0;
+  for (int k = tid; k < 4 * NB16; k += 256) s_b[k] = 0.0f;
+  const int HG = 64 / p.SB, hg = lane / p.SB, sb = lane - hg * p.SB;
+  double acc[kLagBlock];
+#pragma unroll
+  for (int k = 0; k < kLagBlock; ++k) acc[k] = 0.0;
+  const int r0 = chunk * rings, r1 = min(s.nlat, r0 + rings);
+  for (int ring = r0; ring < r1; ++ring) {
+    const int n = bcount[ring];
+    if (n == 0) continue;                            // nothing above the horizon
+    __syncthreads();
+    for (int k = tid; k < n; k += 256) s_l[k] = blist[(size_t)ring * NBk + k];
+    const double omega = s.omega[ring];
+    for (int q = tid; q < nlon; q += 256) {
+      const LagCol v = lag_col<MODE>(s, fb, ring, q);
+      int i, iw = 0;
+      const int cls = lag_class(p, q, i), at = cls * p.HB * kLagBlock + i;
+      const int pa = cls * (p.HB + p.SB) * kLagPad + i + i / kLagBlock;
+      const bool wrap = q < p.smax;                  // the same column a turn on
+      const int cw = wrap ? lag_class(p, q + nlon, iw) : 0;
+      const int pw = cw * (p.HB + p.SB) * kLagPad + iw + iw / kLagBlock;
+      const float b[4] = {v.b.x, v.b.y, v.b.z, v.b.w};
+#pragma unroll
+      for (int ch = 0; ch < 4; ++ch) {
+        const int f = min(4 * fb + ch, s.F - 1);     // no wave reads past the last channel
+        const double a = aval_of<MODE>(s, f, omega, v.t_ex, v.beta);
+        s_b[(size_t)ch * NB16 + at] = b[ch];
+        s_a[(size_t)ch * NA + pa] = a;
+        if (wrap) s_a[(size_t)ch * NA + pw] = a;
+        if (ch & 1) __builtin_amdgcn_sched_barrier(0);   // two powers' registers at a time
+      }
+    }
+    __syncthreads();
+    if (hg < HG && 4 * fb + wave < s.F) {
+      for (int k = hg; k < n; k += HG) {
+        const int2 l = s_l[k];
+        const double* A = s_a + (size_t)wave * NA + l.x + sb * kLagPad;
+        const float4* B = reinterpret_cast<const float4*>(s_b + (size_t)wave * NB16 + l.y);
+        double w[2 * kLagBlock - 1];
+#pragma unroll
+        for (int i = 0; i < 2 * kLagBlock - 1; ++i) w[i] = A[i + i / kLagBlock];
+#pragma unroll
+        for (int j4 = 0; j4 < kLagBlock / 4; ++j4) {
+          const float4 v = B[j4];
+          const double b[4] = {(double)v.x, (double)v.y, (double)v.z, (double)v.w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int u = 0; u < kLagBlock; ++u) acc[u] = fma(b[j], w[4 * j4 + j + u], acc[u]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  double* s_red = s_a + (size_t)wave * 64 * kLagBlock;              // [HG][16 SB]
+  const int NL = kLagBlock * p.SB;
+  if (hg < HG)
+#pragma unroll
+    for (int u = 0; u < kLagBlock; ++u) s_red[hg * NL + sb * kLagBlock + u] = acc[u];
+  __syncthreads();
+  const int f = 4 * fb + wave;
+  if (f >= s.F) return;
+  for (int k = lane; k < NL; k += 64) {
+    double sum = 0.0;
+    for (int h = 0; h < HG; ++h) sum += s_red[h * NL + k];
+    partial[((size_t)chunk * s.F + f) * NL + k] = sum;
+  }
+}
+
+// Per channel and lag: Z, the chunks' sums in order, and W = 1 / Z added up over
+// the lag's steps (step t is steps[k], k in start[lag] .. start[lag + 1] - 1; 0
+// where no step has the lag).  bad[0] becomes the smallest f T + t whose Z is
+// not positive.
+__global__ __launch_bounds__(256) void k_lag_w(const double* __restrict__ partial, int chunks,
+                                               int F, int T, Lag p,
+                                               const int* __restrict__ start,
+                                               const int* __restrict__ steps,
+                                               double* __restrict__ Z, double* __restrict__ W,
+                                               int* __restrict__ bad) {
+  const size_t NL = kLagBlock * p.SB, n = (size_t)F * NL;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int f = (int)(i / NL), lag = (int)(i - f * NL);
+  double z = 0.0;
+#pragma unroll 16
+  for (int c = 0; c < chunks; ++c) z += partial[(size_t)c * n + i];
+  Z[i] = z;
+  double w = 0.0;
+  for (int k = start[lag]; k < start[lag + 1]; ++k) {
+    w += 1.0 / z;
+    if (!(z > 0.0)) atomicMin(bad, (int)min((size_t)f * T + steps[k], (size_t)0x7ffffffe));
+  }
+  W[i] = w;
+}
+
+// imp[(chunk nlat + ring) nlon + q] = sum over the chunk's channels of
+// a(q, f) sum over lags of W(f, lag) b(f, q - g lag): one workgroup per ring and
+// chunk of four-channel blocks.  The ring's tasks (column block x lag block) are
+// spread over the lanes, each task's 16 column totals staying in registers over
+// the channels; 256 / tasks channels of a block run at a time.
+template <int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_lag_imp(SkyDev s, Lag p, const int2* __restrict__ tasks,
+                                                 const int* __restrict__ tstart,
+                                                 const double* __restrict__ W, int bper,
+                                                 double* __restrict__ imp) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int ring = blockIdx.x, chunk = blockIdx.y, nlon = s.nlon, tid = threadIdx.x;
+  const int NBk = p.blocks(), NE = p.ext() * kLagPad, NQ = NBk * kLagPad;
+  const int NW = p.SB * kLagPad, NL = p.SB * kLagBlock, off = p.SB * kLagBlock;
+  int* s_ts = reinterpret_cast<int*>(smem);                         // [NBk + 1] task starts
+  double* s_e = reinterpret_cast<double*>(smem + (NBk + 4) / 4 * 16);   // [4][NE] b at q - lag
+  double* s_q = s_e + 4 * (size_t)NE;                               // [4][NQ] a
+  double* s_w = s_q + 4 * (size_t)NQ;                               // [4][NW] W
+  const int* ts = tstart + (size_t)ring * (NBk + 1);
+  const int n = ts[NBk];
+  const double omega = s.omega[ring];
+  for (int k = tid; k <= NBk; k += 256) s_ts[k] = ts[k];
+  double* out = imp + ((size_t)chunk * s.nlat + ring) * nlon;
+  if (n == 0) {
+    for (int q = tid; q < nlon; q += 256) out[q] = 0.0;
+    return;
+  }
+  const int nb = (s.F + 3) / 4, b0 = chunk * bper, b1 = min(nb, b0 + bper);
+  const int slots = n <= 64 ? 4 : n <= 128 ? 2 : 1, wide = 256 / slots;
+  const int slot = tid / wide, own = tid - slot * wide;
+  for (int first = 0; first < n; first += wide) {    // passes over the ring's tasks
+    const bool live = first + own < n;
+    const int2 task = tasks[(size_t)ring * NBk * p.SB + (live ? first + own : 0)];
+    const int blk = task.y & 0xfffff, sb = task.y >> 20;
+    double tot[kLagBlock];
+#pragma unroll
+    for (int j = 0; j < kLagBlock; ++j) tot[j] = 0.0;
+    __syncthreads();
+    for (int k = tid; k < 4 * (NE + NQ + NW); k += 256) s_e[k] = 0.0;
+    for (int fb = b0; fb < b1; ++fb) {
+      __syncthreads();
+      for (int q = tid; q < nlon; q += 256) {
+        const LagCol v = lag_col<MODE>(s, fb, ring, q);
+        int i, iw = 0;
+        const int cls = lag_class(p, q, i), ie = i + off, blq = cls * p.HB + i / kLagBlock;
+        const int pe = cls * (p.HB + p.SB) * kLagPad + ie + ie / kLagBlock;
+        const int pq = cls * p.HB * kLagPad + i + i / kLagBlock;
+        const bool wrap = q - nlon >= -p.smax;       // the same column a turn back
+        const int cw = wrap ? lag_class(p, q - nlon + p.g * off, iw) : 0;
+        const int pw = cw * (p.HB + p.SB) * kLagPad + iw + iw / kLagBlock;
+        const bool seen = s_ts[blq + 1] > s_ts[blq];  // some task reads this column
+        const float b[4] = {v.b.x, v.b.y, v.b.z, v.b.w};
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) {
+          const int f = min(4 * fb + ch, s.F - 1);
+          s_e[(size_t)ch * NE + pe] = b[ch];
+          if (wrap) s_e[(size_t)ch * NE + pw] = b[ch];
+          const double a = seen ? aval_of<MODE>(s, f, omega, v.t_ex, v.beta) : 0.0;
+          s_q[(size_t)ch * NQ + pq] = 4 * fb + ch < s.F ? a : 0.0;
+          if (ch & 1) __builtin_amdgcn_sched_barrier(0);   // two powers' registers at a time
+        }
+      }
+      for (int k = tid; k < 4 * NL; k += 256) {
+        const int ch = k / NL, l = k - ch * NL, f = min(4 * fb + ch, s.F - 1);
+        s_w[(size_t)ch * NW + l + l / kLagBlock] = W[(size_t)f * NL + l];
+      }
+      __syncthreads();
+      if (!live) continue;
+      for (int ch = slot; ch < 4; ch += slots) {
+        const double* E = s_e + (size_t)ch * NE + task.x + 1;       // q - lag from -15
+        const double* Q = s_q + (size_t)ch * NQ + blk * kLagPad;
+        const double* Wl = s_w + (size_t)ch * NW + sb * kLagPad;
+        double w[2 * kLagBlock - 1], acc[kLagBlock];
+#pragma unroll
+        for (int i = 0; i < 2 * kLagBlock - 1; ++i) w[i] = E[i + (i + 1) / kLagBlock];
+#pragma unroll
+        for (int j = 0; j < kLagBlock; ++j) acc[j] = 0.0;
+#pragma unroll
+        for (int u = 0; u < kLagBlock; ++u) {
+          const double z = Wl[u];
+#pragma unroll
+          for (int j = 0; j < kLagBlock; ++j) acc[j] = fma(z, w[kLagBlock - 1 + j - u], acc[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < kLagBlock; ++j) tot[j] = fma(Q[j], acc[j], tot[j]);
+      }
+    }
+    // this pass's totals: [slot][task][16], then each column adds its tasks and
+    // slots in order (on the earlier passes' sum)
+    __syncthreads();
+    double* s_t = s_e;
+    if (live)
+#pragma unroll
+      for (int j = 0; j < kLagBlock; ++j) s_t[(slot * wide + own) * kLagPad + j] = tot[j];
+    __syncthreads();
+    for (int q = tid; q < nlon; q += 256) {
+      int i;
+      const int c = lag_class(p, q, i), blq = c * p.HB + i / kLagBlock, j = i % kLagBlock;
+      const int k0 = max(s_ts[blq], first), k1 = min(s_ts[blq + 1], first + wide);
+      double sum = first == 0 ? 0.0 : out[q];
+      for (int k = k0; k < k1; ++k)
+        for (int sl = 0; sl < slots; ++sl) sum += s_t[(sl * wide + k - first) * kLagPad + j];
+      out[q] = sum;
+    }
+  }
+}
+
+size_t lag_corr_lds(const Lag& p) {
+  return std::max((size_t)4 * p.ext() * kLagPad * 8 + (size_t)p.blocks() * (4 * kLagBlock * 4 + 8),
+                  (size_t)4 * 64 * kLagBlock * 8);
+}
+size_t lag_imp_lds(const Lag& p) {
+  return ((size_t)p.blocks() + 4) / 4 * 16 +
+         std::max((size_t)4 * (p.ext() + p.blocks() + p.SB) * kLagPad * 8, (size_t)256 * kLagPad * 8);
+}
+
+// The lag grid of a call's shifts, and whether it takes the call: at most 64
+// lag blocks (a wave holds them), the kernels' LDS, and at most four lags per
+// step (of at least 32).  Whole calls on the 256 x 512 sky, 301 channels, by the
+// gather kernels and on the grid (us): 96 steps over 96, 192, 288 and 384 lags
+// 1734 and 635, 1874 and 870, 1871 and 1266, 1954 and 1460; 24 steps over 128
+// lags 1377 and 659; 8 steps over 128 lags 718 and 668.
+bool lag_plan(const int32_t* shifts, int T, int nlon, Lag* out) {
+  Lag p{};
+  int g = 0;
+  for (int t = 0; t < T; ++t) {
+    p.smax = std::max(p.smax, (int)shifts[t]);
+    g = std::gcd(g, (int)shifts[t]);
+  }
+  p.g = std::max(g, 1);
+  p.S = p.smax / p.g + 1;
+  p.SB = (p.S + kLagBlock - 1) / kLagBlock;
+  p.HB = ((nlon + p.g - 1) / p.g + kLagBlock - 1) / kLagBlock;
+  p.inv_g = p.g > 1 ? (unsigned)(((1ull << 32) + p.g - 1) / p.g) : 0u;
+  *out = p;
+  return p.SB <= 64 && p.SB * kLagBlock <= 4 * pad_to(T, 32) && p.blocks() < 1 << 20 &&
+         (size_t)p.blocks() + p.ext() <= 64 * 1024 && lag_corr_lds(p) <= 160 * 1024 &&
+         lag_imp_lds(p) <= 160 * 1024;
+}
+
 // LDS of a k_sky_corr workgroup: the four channels' weights (Lz columns) and
 // the window of nlon + smax + 8 four-channel b columns.
 size_t corr_lds(int nlon, int smax, int Lz) {
   return (size_t)Lz * 32 + ((size_t)nlon + smax + 8) * 16;
 }
-
-int pad8(int n) { return (n + 7) / 8 * 8; }
-int pad4(int n) { return (n + 3) / 4 * 4; }
-
 
 struct Sky {
   int dev = 0;
@@ -497,6 +863,80 @@ int run_corr(Sky* sk, const int* d_shifts, int T, int smax, int Lz, double* d_ou
   if (e == hipSuccess) e = hipStreamSynchronize(sk->stream);
   (void)hipFree(part);
   return e == hipSuccess ? FGL_OK : hip_err(e, "normaliser kernels");
+}
+
+// Importance on the lag grid p into `importance` (host): the block lists, the
+// normalisers and step weights and the map, queued on the sky's stream.
+constexpr int kLagRings = 4;           // rings per k_lag_corr workgroup
+constexpr int kLagGroups = 4096;       // k_lag_imp workgroups aimed at
+template <int MODE>
+int run_lag(Sky* sk, const Lag& p, const int32_t* shifts, int T, double* importance) {
+  const SkyDev& d = sk->d;
+  const int NBk = p.blocks(), NT = NBk * p.SB, NL = kLagBlock * p.SB, nb = (d.F + 3) / 4;
+  const int chunks = (d.nlat + kLagRings - 1) / kLagRings;
+  const int fch = std::max(1, std::min(nb, (kLagGroups + d.nlat - 1) / d.nlat));
+  const int bper = (nb + fch - 1) / fch, nch = (nb + bper - 1) / bper;
+  const size_t np = (size_t)d.nlat * d.nlon, nw = (size_t)d.F * NL;
+  // the steps of each lag, after one word for the first bad normaliser
+  const int none = 0x7fffffff;
+  std::vector<int> h(1 + NL + 1 + T, 0);
+  h[0] = none;
+  int *h_start = &h[1], *h_steps = h_start + NL + 1;
+  for (int t = 0; t < T; ++t) ++h_start[shifts[t] / p.g + 1];
+  std::partial_sum(h_start, h_start + NL + 1, h_start);
+  std::vector<int> at(h_start, h_start + NL);
+  for (int t = 0; t < T; ++t) h_steps[at[shifts[t] / p.g]++] = t;
+  struct Bufs {
+    void* p[8] = {};
+    ~Bufs() {
+      for (void* q : p)
+        if (q) (void)hipFree(q);
+    }
+  } m;
+  const size_t need[8] = {(size_t)d.nlat * NBk * sizeof(int2), (size_t)d.nlat * sizeof(int),
+                          (size_t)d.nlat * NT * sizeof(int2), (size_t)d.nlat * (NBk + 1) * sizeof(int),
+                          std::max(nw * chunks, np * nch) * 8, 2 * nw * 8, np * 8,
+                          h.size() * sizeof(int)};
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < 8 && e == hipSuccess; ++k) e = hipMalloc(&m.p[k], need[k]);
+  if (e != hipSuccess) return hip_err(e, "allocating importance buffers");
+  int2 *blist = static_cast<int2*>(m.p[0]), *tasks = static_cast<int2*>(m.p[2]);
+  int *bcount = static_cast<int*>(m.p[1]), *tstart = static_cast<int*>(m.p[3]);
+  double *part = static_cast<double*>(m.p[4]), *Z = static_cast<double*>(m.p[5]), *W = Z + nw;
+  double* imp = static_cast<double*>(m.p[6]);
+  int *bad = static_cast<int*>(m.p[7]), *start = bad + 1, *steps = start + NL + 1;
+  hipStream_t st = sk->stream;
+  if ((e = set_lds(k_lag_corr<MODE>)) == hipSuccess) e = set_lds(k_lag_imp<MODE>);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(bad, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice, st);
+  if (e != hipSuccess) return hip_err(e, "importance kernels");
+  hipLaunchKernelGGL(k_lag_blocks, dim3(d.nlat), dim3(64), NBk + p.ext(), st, d, p, blist, bcount,
+                     tasks, tstart);
+  hipLaunchKernelGGL(k_lag_corr<MODE>, dim3(nb, chunks), dim3(256), lag_corr_lds(p), st, d, p,
+                     blist, bcount, kLagRings, part);
+  hipLaunchKernelGGL(k_lag_w, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, part, chunks,
+                     d.F, T, p, start, steps, Z, W, bad);
+  hipLaunchKernelGGL(k_lag_imp<MODE>, dim3(d.nlat, nch), dim3(256), lag_imp_lds(p), st, d, p,
+                     tasks, tstart, W, bper, part);
+  hipLaunchKernelGGL(k_sky_reduce, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, part, nch,
+                     np, imp);
+  int first = none;
+  if ((e = hipGetLastError()) == hipSuccess &&
+      (e = hipMemcpyAsync(importance, imp, np * 8, hipMemcpyDeviceToHost, st)) == hipSuccess &&
+      (e = hipMemcpyAsync(&first, bad, 4, hipMemcpyDeviceToHost, st)) == hipSuccess)
+    e = hipStreamSynchronize(st);
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(st);
+    return hip_err(e, "importance kernels");
+  }
+  if (first != none) {
+    const int f = first / T, t = first % T;
+    double z = 0.0;
+    if ((e = hipMemcpy(&z, Z + (size_t)f * NL + shifts[t] / p.g, 8, hipMemcpyDeviceToHost)) != hipSuccess)
+      return hip_err(e, "copy normalisers");
+    return set_err(FGL_EINVAL, "the weight of channel %d, step %d integrates to %g", f, t, z);
+  }
+  return FGL_OK;
 }
 
 // LDS of a k_sky_k workgroup: two buffers of the row window (nlon + smax
@@ -785,11 +1225,18 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
   const int smax = *std::max_element(shifts, shifts + T);
   if (corr_lds(sk->d.nlon, smax, Lz) > 160 * 1024)
     return set_err(FGL_EINVAL, "nlon=%d does not fit one workgroup's LDS", sk->d.nlon);
+  const size_t imp_lds = (size_t)T * 36 + (size_t)sk->d.nlon * 32;
+  Lag lag;
+  const bool on_grid = imp_lds <= 160 * 1024 && lag_plan(shifts, T, sk->d.nlon, &lag);
   hipError_t e = hipSetDevice(sk->dev);
   if (e != hipSuccess) return hip_err(e, "hipSetDevice");
   const SkyDev& d = sk->d;
   int* d_sh = nullptr;
   double *Z = nullptr, *imp = nullptr;
+  if (on_grid)
+    return scheme == FGL_WEIGHT_BEAM ? run_lag<kCorrBeam>(sk, lag, shifts, T, importance)
+           : scheme == FGL_WEIGHT_SKY ? run_lag<kCorrSky>(sk, lag, shifts, T, importance)
+                                      : run_lag<kCorrHorizon>(sk, lag, shifts, T, importance);
   if ((rc = to_device(&d_sh, shifts, (size_t)T, "uploading shifts")) != FGL_OK) return rc;
   if ((e = hipMalloc(reinterpret_cast<void**>(&Z), (size_t)d.F * T * 8)) != hipSuccess ||
       (e = hipMalloc(reinterpret_cast<void**>(&imp), (size_t)d.nlat * d.nlon * 8)) != hipSuccess) {
@@ -810,7 +1257,6 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
                      k / T, k % T, hz[k]);
   }
   if (rc == FGL_OK) {
-    const size_t lds = (size_t)T * 36 + (size_t)d.nlon * 32;
     // chunks of four-channel blocks: enough workgroups to fill the device,
     // summed in order
     const int nb = (d.F + 3) / 4;
@@ -819,7 +1265,7 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
     const int nch = (nb + bper - 1) / bper;
     const size_t np = (size_t)d.nlat * d.nlon;
     double* part = nullptr;
-    if (lds > 160 * 1024) {
+    if (imp_lds > 160 * 1024) {
       rc = set_err(FGL_EINVAL, "T=%d and nlon=%d do not fit one workgroup's LDS", T, d.nlon);
     } else if ((e = hipMalloc(reinterpret_cast<void**>(&part), np * nch * 8)) != hipSuccess) {
       rc = hip_err(e, "allocating importance partials");
@@ -827,7 +1273,7 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
       auto launch = [&](auto kern) {
         hipError_t ee = set_lds(kern);
         if (ee != hipSuccess) return ee;
-        hipLaunchKernelGGL(kern, dim3(d.nlat, nch), dim3(256), lds, sk->stream, d, d_sh, T, Z,
+        hipLaunchKernelGGL(kern, dim3(d.nlat, nch), dim3(256), imp_lds, sk->stream, d, d_sh, T, Z,
                            bper, part);
         return hipGetLastError();
       };
