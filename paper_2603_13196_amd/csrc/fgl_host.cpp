@@ -131,6 +131,21 @@ static inline uint32_t digits4(int32_t q) {
 
 static void build_projected(Model* m, const float* K, const double* data);
 
+// Region of slot j of lane half g of chunk kc in the mixed digits, or -1, at
+// [kc * 32 + g * 16 + j].
+static std::vector<int> mixed_regions(const DevModel& d) {
+  const bool sh = mixed_short_chunk(d.N, d.ng, d.KC, d.proj != 0, mixed_alpha_mode(d));
+  std::vector<int> at(d.KC * 32, -1);
+  for (int kc = 0; kc < d.KC; ++kc) {
+    const int end = kc + 1 < d.KC ? std::min(d.N, mixed_chunk(kc + 1, d.ng, sh)) : d.N;
+    for (int g = 0; g < 2; ++g)
+      for (int j = 0; j < 4 * d.ng; ++j) {
+        const int i = mixed_chunk(kc, d.ng, sh) + g * 4 * d.ng + j;
+        if (i < end) at[kc * 32 + g * 16 + j] = i;
+      }
+  }
+  return at;
+}
 
 // 2^(r/64) on |r| <= 1/2 for the mixed kernel: the degree-4 polynomial that
 // interpolates it at the five Chebyshev nodes (monomial coefficients q[0..4],
@@ -176,6 +191,7 @@ static void build_layouts(Model* m, const float* K, const double* freqs,
   // bound behind the int32 level sums of the mixed kernel); if rounding
   // reaches 126 2^24 the channel uses eK + 1.  K values within 2^8 of the
   // channel's largest are exact.
+  const std::vector<int> slots = mixed_regions(m->dm);
   m->h_kd.assign((size_t)F * 4 * KC * TT * 1024, 0);
   m->h_eK.assign(F, 0);
   for (int f = 0; f < F; ++f) {
@@ -194,10 +210,10 @@ static void build_layouts(Model* m, const float* K, const double* freqs,
       for (int tt = 0; tt < TT; ++tt)
         for (int lane = 0; lane < 64; ++lane)
           for (int j = 0; j < 16; ++j) {
-            const int i = kc * 32 + (lane >> 5) * 16 + j;
+            const int i = slots[kc * 32 + (lane >> 5) * 16 + j];
             const int t = tt * 32 + (lane & 31);
             uint32_t d = 0x00000000u;
-            if (i < N && t < T) {
+            if (i >= 0 && t < T) {
               const double v = std::ldexp((double)Kat(i, f, t), 31 - ek);
               d = digits4((int32_t)std::nearbyint(v));
             }
@@ -293,6 +309,7 @@ static void build_projected(Model* m, const float* K, const double* data) {
   const int KC = d.KC, RT = d.RT;
   const int rows = d.peel ? N : N + 1;              // rows in MFMA tiles
   const long double sT = std::sqrt((long double)T);
+  const std::vector<int> slots = mixed_regions(d);
   m->h_rd.assign((size_t)F * kProjDigits * KC * RT * 1024, 0);
   if (d.pplain) m->h_r32.assign((size_t)F * d.NP2 * RT * 64, 0.0f);
   m->h_eR.assign(F, 0);
@@ -389,10 +406,10 @@ static void build_projected(Model* m, const float* K, const double* data) {
       for (int rt = 0; rt < RT; ++rt)
         for (int lane = 0; lane < 64; ++lane)
           for (int j = 0; j < 16; ++j) {
-            const int i = kc * 32 + (lane >> 5) * 16 + j;
+            const int i = slots[kc * 32 + (lane >> 5) * 16 + j];
             const int k = rt * 32 + (lane & 31);
             int8_t dg[6] = {0, 0, 0, 0, 0, 0};
-            if (i < N && k < rows) {
+            if (i >= 0 && k < rows) {
               const long double v = std::ldexp(mat[(size_t)k * N + i], kProjBits - er);
               digits6(std::llrint(v), dg);
             }
@@ -1058,6 +1075,7 @@ static int create_model(const float* K, const double* freqs, const double* data,
       d.peel = peel;
     }
   }
+  d.ng = mixed_groups(d);
   d.pplain = (d.proj && (flags & FGL_PLAIN_PROJECTED)) ? 1 : 0;
   for (Kind k : {kMixed, kFP32, kFP64, kThin}) {
     if (k == kThin && !d.thin) continue;

@@ -153,6 +153,7 @@ struct DevModel {
   int TT;            // 32-row time tiles (mixed, FP32)
   int TT16;          // 16-row time tiles (FP64)
   int KC;            // 32-region chunks (mixed)
+  int ng;            // 4-region groups a lane holds per chunk (mixed; mixed_groups)
   int NP2;           // region pairs, rounded up to a compiled size (FP32)
   int NQ;            // region quads, rounded up to a compiled size (FP64)
   double t_cmb;
@@ -204,6 +205,32 @@ struct DevModel {
 // (one alpha per region).
 inline int mixed_alpha_mode(const DevModel& d) {
   return d.NA == 0 ? 0 : (d.NB % 16 == 0 ? 2 : 1);
+}
+// Where the mixed kernel keeps its regions: KC chunks of two lane halves of
+// 4 ng slots each, ng as small as holds N, so that a lane does not evaluate the
+// powers of slots no region needs (half-chunks keep 16 slots where a lane holds
+// one alpha for them).  Chunk kc starts at region mixed_chunk(kc).
+inline int mixed_groups(const DevModel& d) {
+  const int slots = 8 * d.KC;                       // slots per group of four
+  return mixed_alpha_mode(d) == 2 ? 4 : (d.N + slots - 1) / slots;
+}
+// In the projected form row k > 0 of the matrix is zero below region k - 1, so
+// row tile tt > 0 needs no chunk that ends at region 32 tt - 2 or before: the
+// kernel then leaves out the chunks before tt.  It does so for two chunks (one
+// alpha per region: where a lane holds fewer than 16) and for three of 12 slots;
+// past that its unrolled tiles spill (0.57-0.65x the rolled loop's speed at 60
+// regions with masks and 80-96 without).
+__host__ __device__ constexpr bool mixed_skips(int ng, int KC, int alpha_mode) {
+  return KC == 1 || ng < 4 || (KC == 2 && alpha_mode != 1);
+}
+// For that the first of two chunks of 32 slots takes 31 regions where the other
+// has room for the rest.
+__host__ __device__ inline bool mixed_short_chunk(int N, int ng, int KC, bool proj,
+                                                  int alpha_mode) {
+  return proj && KC == 2 && ng == 4 && alpha_mode == 0 && N < 64;
+}
+__host__ __device__ inline int mixed_chunk(int kc, int ng, bool short_chunk) {
+  return kc * 8 * ng - (kc > 0 && short_chunk ? 1 : 0);
 }
 // The mixed kernel's three-waves-per-SIMD compile exists for the projected
 // form with one region chunk and at most one alpha per lane and chunk.

@@ -153,54 +153,62 @@ __device__ inline double gauss21(double nu, const RowParams& rp) {
 // last row of R (a single diagonal entry) is evaluated in FP64 from the
 // same rounded power, so the MFMA rows fill whole tiles.
 
-// OCC: waves per SIMD the register allocation targets (2, or 3 for the
-// projected form with one region chunk, which fits in 168 registers).
-// The body of workgroup `block` of a launch on (m, w); the kernels below
-// call it for one model (k_mixed) or for several that share the compiled
-// variant (k_mixed_multi).
-template <int W, int KC, bool PROJ, int OCC, int AM>
-__device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, const Chunks& cp,
-                                           int G, int nb, int block) {
+// Padding is left out where it costs vector work: a lane evaluates only the
+// powers of the slots that hold regions (4, 8, 12 or 16 per chunk), the last row
+// tile's epilogue stops after its last group of eight rows, and in the projected
+// form a row tile leaves out the chunks that are zero for it (R is upper
+// triangular).  The kernel is bound by vector issue, the powers and the epilogue
+// being its two largest blocks, so it follows what is left out; whole calls at
+// 301 channels and 16384 rows (us, all padding computed, and now):
+//   projected, 96 bins   N 10 176, 122   N 16 179, 133   N 21 183, 153
+//                        N 24 184, 162   N 32 197, 191   N 40 538, 414
+//   direct               N 40 T 30 464, 307              N 16 T 28 230, 189
+//   N 64, 401 channels, 240 bins: 733, 673 (63 products of 84 a channel)
+// N = 32 has nothing to leave out; its gain is the shorter code of a loop that
+// is compiled for one slot count.  The sums are integers: leaving out zeros
+// changes no bit (the entry done in FP64 at N = 64 rounds once differently).
+
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+// The channels f0 .. f0 + fn - 1 of one row tile, by a wave whose lanes hold NG
+// groups of four regions per chunk (staged operands in LDS; ND matrix digits).
+// JQ: groups of eight rows that are not all padding, for the projected form with
+// one chunk (the other forms find their last tile's at run time: the branch
+// costs them nothing, and compiled apart their loops spilled more).
+template <int KC, bool PROJ, int AM, int NG, int JQ>
+__device__ __forceinline__ void mixed_channels(const DevModel& m, const Work& w, int G, int f0,
+                                               int fn, int b, const double* s_tab,
+                                               const unsigned char* s_kd, const double* s_D) {
   constexpr int ND = PROJ ? kProjDigits : 4;       // digits of the matrix rows
   constexpr int NP = 6;                            // digits of the powers
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int bt, ch;
-  map_block_split(block, nb, cp.nbig, cp.nc - cp.nbig, bt, ch);
+  constexpr int NJ = 4 * NG;                       // regions a lane holds per chunk
+  const int lane = threadIdx.x & 63, g = lane >> 5;
   const int TT = PROJ ? m.RT : m.TT;               // 32-row tiles
-  const int fc = cp.fc;                            // LDS layout: the large chunk
-  const bool big = ch < cp.nbig;
-  const int f0 = big ? ch * fc : cp.nbig * fc + (ch - cp.nbig) * cp.fs;
-  const int fn = min(big ? fc : cp.fs, m.F - f0);
   const int kbytes = ND * KC * TT * 1024;
-  // LDS: the exponent tables at offset 0 (so a table byte offset is an LDS
-  // address), then the channels' matrix digits and data
-  double* s_tab = reinterpret_cast<double*>(smem);
-  unsigned char* s_kd = smem + kTabBytes;
-  double* s_D = reinterpret_cast<double*>(s_kd + (size_t)fc * kbytes);
-  stage(s_tab, m.tab, kTabBytes);
-  stage(s_kd, (PROJ ? m.rd : m.kd) + (size_t)f0 * kbytes, fn * kbytes);
-  stage(s_D, (PROJ ? m.tg : m.D) + (size_t)f0 * TT * 32, fn * TT * 32 * 8);
-  __syncthreads();
   const double* s_tab0 = s_tab + kTabLo;            // s_tab0[jj], jj in [-kTabLo, 0]
   const double* s_frac = s_tab + kTabSize;          // unit of the level-0 product
   const double* s_ifrac = s_frac + kFracSize;       // its reciprocal
-
-  const int g = lane >> 5;
-  const int b = bt * (W * 32) + wave * 32 + (lane & 31);
   const RowParams rp = w.rows[b];
   // amplitude masks (AM): 64 log2 alpha per region (AM = 1), or one value
   // per 16-region half chunk when the index masks come in multiples of 16,
   // so that each half chunk lies within one amplitude mask (AM = 2)
   constexpr bool AB = AM != 0;
-  double beta[KC][16];
-  double off[AM == 1 ? KC : 1][16];
+  const bool short_chunk = mixed_short_chunk(m.N, NG, KC, PROJ, AM);
+  // row tiles leave out the chunks that are zero for them, where the unrolled
+  // tiles fit the registers
+  constexpr bool SKIP = PROJ && mixed_skips(NG, KC, AM);
+  // a full first chunk leaves the second tile one entry in it: region 31 of the
+  // tile's first row, done in FP64
+  constexpr bool DIAG = SKIP && KC == 2 && NG == 4;
+  double beta[KC][NJ];
+  double off[AM == 1 ? KC : 1][NJ];
   double off1[AM == 2 ? KC : 1];
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const size_t at = (size_t)(kc * 32 + g * 16 + j) * w.Bpad + b;
+    for (int j = 0; j < NJ; ++j) {
+      const size_t at = (size_t)(mixed_chunk(kc, NG, short_chunk) + g * NJ + j) * w.Bpad + b;
       beta[kc][j] = w.betaT[at];
       if constexpr (AM == 1) off[kc][j] = 64.0 * w.offT[at];
       if constexpr (AM == 2)
@@ -218,10 +226,12 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
   // b, 16 regions per 32-region chunk, five significance levels).
   struct Scal {
     double nl, nu;
+    double rd;                 // the entry done in FP64
     int ek;
   };
   struct Epi {                 // what the epilogue and the peeled row need
     double s0, t0, qlast;      // s0: unit of acc0 (acc1: s0 2^-16, acc2: s0 2^-32)
+    double dt;                 // its term
     int ey, fm;
   };
   struct Chan {
@@ -231,7 +241,14 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
   };
   auto fetch = [&](int fi) {
     const int fx = min(fi, m.F - 1);
-    return Scal{m.nl64[fx], m.nu[fx], PROJ ? m.eR[fx] : m.eK[fx]};
+    Scal sc;
+    sc.nl = m.nl64[fx];
+    sc.nu = m.nu[fx];
+    sc.ek = PROJ ? m.eR[fx] : m.eK[fx];
+    if constexpr (DIAG)
+      if (!short_chunk)                            // row 32, region 31 of the FP64 rows
+        sc.rd = m.pa64[(((size_t)fx * m.NQ + 7) * m.RT16 + 2) * 64 + 48];
+    return sc;
   };
   auto make = [&](const Scal& sc, int fi, Chan& C) {
     const double nl = sc.nl;
@@ -299,9 +316,9 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
     const double cm = MAGIC - ymax;                 // exact: ymax is an integer
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
-      uint32_t lo[16], hi[16];
+      uint32_t lo[NJ], hi[NJ];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         double t, r;
         if constexpr (AB) {
           const double y = fma(beta[kc][j], nl, AM == 1 ? off[kc][j] : off1[kc]) - ymax;
@@ -322,12 +339,14 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
         p = fma(r, p, m.q[0]);                     // 2^(r/64), degree 4
         const double q = fma(T2, p, DIGITS);       // 2^52 + q + offsets
         if (PROJ && kc == KC - 1 && j == 15) C.e.qlast = q - DIGITS;
+        if constexpr (DIAG)
+          if (kc == 0 && j == 15) C.e.dt = q - DIGITS;
         const unsigned long long bits = __double_as_longlong(q);
         lo[j] = (uint32_t)bits ^ 0x80808080u;      // digits d2 d3 d4 d5 (byte 3..0)
         hi[j] = (uint32_t)(bits >> 32);            // byte 1: d0, byte 0: d1 + 128
       }
 #pragma unroll
-      for (int m4 = 0; m4 < 4; ++m4) {
+      for (int m4 = 0; m4 < NG; ++m4) {
         uint32_t o[4];
         transpose4(lo[4 * m4], lo[4 * m4 + 1], lo[4 * m4 + 2], lo[4 * m4 + 3], o);
         // o[L] holds byte (3 - L) of the low words: d(L+2)
@@ -341,48 +360,63 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
         C.B[kc][1][m4] = (int32_t)(__builtin_amdgcn_perm(y, x, 0x06040200u) ^ 0x80808080u);
         C.B[kc][0][m4] = (int32_t)__builtin_amdgcn_perm(y, x, 0x07050301u);
       }
+#pragma unroll
+      for (int m4 = NG; m4 < 4; ++m4)              // slots without a region
+#pragma unroll
+        for (int p = 0; p < NP; ++p) C.B[kc][p][m4] = 0;
     }
+    if constexpr (DIAG)
+      // to the lane half that holds the first row
+      C.e.dt = short_chunk ? 0.0 : ldexp(s_frac[fm], ey - 47) * sc.rd * __shfl_xor(C.e.dt, 32);
   };
 
-  auto load_A = [&](int f, int tt, i32x4 (&A)[ND][KC]) {
+  // Row tile tt: its products with chunks K0 and up (tile tt > 0 of the projected
+  // form has none with the chunks before), and the residuals of its first QN
+  // groups of eight rows (a later group holds padding only, whose sums and
+  // targets are zero).  QN = 0: `jq` groups (direct form: rows past T masked).
+  //
+  // MF(acc, q, p): the product of matrix digit q and power digit p
+#define MF(acc, q, p) \
+  acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[q][kc - K0], C.B[kc][p], acc, 0, 0, 0)
+  auto tile = [&](int f, int tt, const Chan& C, auto k0, auto qn, int jq = 4) {
+    constexpr int K0 = decltype(k0)::value, QN = decltype(qn)::value;
+    constexpr int QM = QN > 0 ? QN : 4;
+    i32x4 A[ND][KC - K0];
     const unsigned char* kf = s_kd + (size_t)f * kbytes + lane * 16;
 #pragma unroll
     for (int L = 0; L < ND; ++L)
 #pragma unroll
-      for (int kc = 0; kc < KC; ++kc)
-        A[L][kc] = *reinterpret_cast<const i32x4*>(kf + ((L * KC + kc) * TT + tt) * 1024);
-  };
-  // MF(acc, q, p): the product of matrix digit q and power digit p
-#define MF(acc, q, p) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[q][kc], C.B[kc][p], acc, 0, 0, 0)
-  // levels 0, 2 and 4 (no dependence on a shift)
-  auto part1 = [&](const i32x4 (&A)[ND][KC], const Chan& C, i32x16& a0, i32x16& a1,
-                   i32x16& a2) {
-    a0 = i32x16{};
-    a1 = i32x16{};
-    a2 = i32x16{};
+      for (int kc = K0; kc < KC; ++kc)
+        A[L][kc - K0] = *reinterpret_cast<const i32x4*>(kf + ((L * KC + kc) * TT + tt) * 1024);
+    // levels 0, 2 and 4 (no dependence on a shift)
+    i32x16 a0 = {}, a1 = {}, a2 = {};
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
+    for (int kc = K0; kc < KC; ++kc) {
       MF(a0, 0, 0);
       MF(a1, 0, 2); MF(a1, 1, 1); MF(a1, 2, 0);
       MF(a2, 0, 4); MF(a2, 1, 3); MF(a2, 2, 2); MF(a2, 3, 1);
       if constexpr (PROJ) MF(a2, 4, 0);
     }
-  };
-  // shift-adds (direct form: with the constant term's digits), then levels
-  // 1, 3 and 5
-  auto part2 = [&](const i32x4 (&A)[ND][KC], const Chan& C, i32x16& a0, i32x16& a1,
-                   i32x16& a2) {
-    if constexpr (PROJ) {
-      a0 = (i32x16)((u32x16)a0 << 8u);
-      a1 = (i32x16)((u32x16)a1 << 8u);
-      a2 = (i32x16)((u32x16)a2 << 8u);
+    // shift-adds (direct form: with the constant term's digits), then levels
+    // 1, 3 and 5
+    if constexpr (QN == 4) {
+      a0 = (i32x16)(((u32x16)a0 << 8u) + (PROJ ? 0u : (uint32_t)C.c0));
+      a1 = (i32x16)(((u32x16)a1 << 8u) + (PROJ ? 0u : (uint32_t)C.c1));
+      a2 = (i32x16)(((u32x16)a2 << 8u) + (PROJ ? 0u : (uint32_t)C.c2));
     } else {
-      a0 = (i32x16)(((u32x16)a0 << 8u) + (uint32_t)C.c0);
-      a1 = (i32x16)(((u32x16)a1 << 8u) + (uint32_t)C.c1);
-      a2 = (i32x16)(((u32x16)a2 << 8u) + (uint32_t)C.c2);
+#pragma unroll
+      for (int q = 0; q < QM; ++q) {
+        if (QN == 0 && q >= jq) break;
+#pragma unroll
+        for (int j = 4 * q; j < 4 * q + 4; ++j) {
+          a0[j] = (int32_t)(((uint32_t)a0[j] << 8) + (PROJ ? 0u : (uint32_t)C.c0));
+          a1[j] = (int32_t)(((uint32_t)a1[j] << 8) + (PROJ ? 0u : (uint32_t)C.c1));
+          a2[j] = (int32_t)(((uint32_t)a2[j] << 8) + (PROJ ? 0u : (uint32_t)C.c2));
+        }
+      }
     }
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
+    for (int kc = K0; kc < KC; ++kc) {
       MF(a0, 0, 1); MF(a0, 1, 0);
       MF(a1, 0, 3); MF(a1, 1, 2); MF(a1, 2, 1); MF(a1, 3, 0);
       MF(a2, 0, 5); MF(a2, 1, 4); MF(a2, 2, 3); MF(a2, 3, 2);
@@ -390,38 +424,36 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
         MF(a2, 4, 1); MF(a2, 5, 0);
       }
     }
-  };
-#undef MF
-  auto epi = [&](int f, int tt, const Epi& C, const i32x16& a0, const i32x16& a1,
-                 const i32x16& a2) {
+    // epilogue: residuals and chi-square
     const double* Dt = s_D + (size_t)f * TT * 32 + g * 4 + tt * 32;
-    const double s0 = C.s0, s1 = C.s0 * 0x1.0p-16, s2 = C.s0 * 0x1.0p-32;
-    if (!PROJ && tt == TT - 1 && (m.T & 31)) {     // ragged last tile (uniform)
+    const double s0 = C.e.s0, s1 = C.e.s0 * 0x1.0p-16, s2 = C.e.s0 * 0x1.0p-32;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        double r = fma(-s0, (double)a0[j], Dt[(j >> 2) * 8 + (j & 3)]);
-        r = fma(-s1, (double)a1[j], r);
-        r = fma(-s2, (double)a2[j], r);
-        const int t = tt * 32 + (j >> 2) * 8 + g * 4 + (j & 3);
-        r = t < m.T ? r : 0.0;
-        if (j & 1) acc_b = fma(r, r, acc_b);
-        else acc_a = fma(r, r, acc_a);
-      }
-    } else {
+    for (int q = 0; q < QM; ++q) {
+      if (QN == 0 && q >= jq) break;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
+      for (int j = 4 * q; j < 4 * q + 4; ++j) {
         double d = Dt[(j >> 2) * 8 + (j & 3)];
-        // projected form: row 0 (element 0 of the first tile in lanes
-        // 0..31) is the mean row, whose target depends on the row b
-        if (PROJ && j == 0) d = (tt == 0 && g == 0) ? C.t0 : d;
+        // projected form: row 0 (element 0 of the first tile in lanes 0..31) is
+        // the mean row, whose target depends on the row b; the first rows of
+        // later tiles have a term in FP64
+        if constexpr (PROJ)
+          if (j == 0) {
+            if constexpr (K0 > 0) d = DIAG && g == 0 ? d - C.e.dt : d;
+            else d = tt == 0 && g == 0 ? C.e.t0 : d;
+          }
         double r = fma(-s0, (double)a0[j], d);
         r = fma(-s1, (double)a1[j], r);
         r = fma(-s2, (double)a2[j], r);
+        if constexpr (!PROJ && QN == 0) {
+          const int t = tt * 32 + (j >> 2) * 8 + g * 4 + (j & 3);
+          r = t < m.T ? r : 0.0;
+        }
         if (j & 1) acc_b = fma(r, r, acc_b);
         else acc_a = fma(r, r, acc_a);
       }
     }
   };
+#undef MF
   // after a channel's last row tile: the peeled row, the partial
   auto tail = [&](int f, const Epi& C) {
     if constexpr (PROJ) {
@@ -446,29 +478,97 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
 
   // A wave finishes one row tile before the next; the other waves of its
   // SIMD overlap their vector work with its matrix work.
+  const int jq = (m.N + 1 - m.peel - 32 * (KC - 1) + 7) >> 3;   // projected form
   Scal sc = fetch(f0);
   for (int f = 0; f < fn; ++f) {
     const Scal cur = sc;
     sc = fetch(f0 + f + 1);                        // one channel ahead
     Chan C;
     make(cur, f0 + f, C);
-    for (int tt = 0; tt < TT; ++tt) {
-      i32x4 A[ND][KC];
-      i32x16 x0, x1, x2;
-      load_A(f, tt, A);
-      part1(A, C, x0, x1, x2);
-      part2(A, C, x0, x1, x2);
-      epi(f, tt, C.e, x0, x1, x2);
+    if constexpr (PROJ) {                          // KC row tiles
+      if constexpr (KC == 1) {
+        tile(f, 0, C, Int<0>{}, Int<JQ>{});
+      } else if constexpr (!SKIP) {
+        for (int tt = 0; tt < TT; ++tt) tile(f, tt, C, Int<0>{}, Int<4>{});
+      } else {
+        tile(f, 0, C, Int<0>{}, Int<4>{});
+        if constexpr (KC > 2) tile(f, 1, C, Int<1>{}, Int<4>{});
+        if (jq < 4) tile(f, KC - 1, C, Int<KC - 1>{}, Int<0>{}, jq);
+        else tile(f, KC - 1, C, Int<KC - 1>{}, Int<4>{});
+      }
+    } else {
+      for (int tt = 0; tt < TT - 1; ++tt) tile(f, tt, C, Int<0>{}, Int<4>{});
+      if (m.T & 31)
+        tile(f, TT - 1, C, Int<0>{}, Int<0>{}, (m.T - 32 * (TT - 1) + 7) >> 3);
+      else
+        tile(f, TT - 1, C, Int<0>{}, Int<4>{});
     }
     tail(f, C.e);
   }
 }
 
-template <int W, int KC, bool PROJ, int OCC, int AM>
+// OCC: waves per SIMD the register allocation targets (2, or 3 for the
+// projected form with one region chunk, which fits in 168 registers).
+// The body of workgroup `block` of a launch on (m, w); the kernels below
+// call it for one model (k_mixed) or for several that share the compiled
+// variant (k_mixed_multi).
+template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0>
+__device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, const Chunks& cp,
+                                           int G, int nb, int block) {
+  constexpr int ND = PROJ ? kProjDigits : 4;       // digits of the matrix rows
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int bt, ch;
+  map_block_split(block, nb, cp.nbig, cp.nc - cp.nbig, bt, ch);
+  const int TT = PROJ ? m.RT : m.TT;               // 32-row tiles
+  const int fc = cp.fc;                            // LDS layout: the large chunk
+  const bool big = ch < cp.nbig;
+  const int f0 = big ? ch * fc : cp.nbig * fc + (ch - cp.nbig) * cp.fs;
+  const int fn = min(big ? fc : cp.fs, m.F - f0);
+  const int kbytes = ND * KC * TT * 1024;
+  // LDS: the exponent tables at offset 0 (so a table byte offset is an LDS
+  // address), then the channels' matrix digits and data
+  double* s_tab = reinterpret_cast<double*>(smem);
+  unsigned char* s_kd = smem + kTabBytes;
+  double* s_D = reinterpret_cast<double*>(s_kd + (size_t)fc * kbytes);
+  stage(s_tab, m.tab, kTabBytes);
+  stage(s_kd, (PROJ ? m.rd : m.kd) + (size_t)f0 * kbytes, fn * kbytes);
+  stage(s_D, (PROJ ? m.tg : m.D) + (size_t)f0 * TT * 32, fn * TT * 32 * 8);
+  __syncthreads();
+  const int b = bt * (W * 32) + wave * 32 + (lane & 31);
+  auto run = [&](auto ng, auto jq) {
+    mixed_channels<KC, PROJ, AM, decltype(ng)::value, decltype(jq)::value>(m, w, G, f0, fn, b,
+                                                                           s_tab, s_kd, s_D);
+  };
+  // groups of four regions per lane and chunk and, for one chunk (8 NG + 1 rows
+  // at most), of eight rows: each as its own loop, since a choice inside the loop
+  // costs registers and the three-wave compile has none left
+  const int rows = m.N + 1 - m.peel;
+  if constexpr (NG > 0) {
+    run(Int<NG>{}, Int<4>{});
+  } else if constexpr (AM == 2 || KC == 4) {
+    run(Int<4>{}, Int<4>{});
+  } else if constexpr (PROJ && KC == 1) {
+    if (m.ng == 4) run(Int<4>{}, Int<4>{});
+    else if (m.ng == 3) rows <= 24 ? run(Int<3>{}, Int<3>{}) : run(Int<3>{}, Int<4>{});
+    else if (m.ng == 2) rows <= 16 ? run(Int<2>{}, Int<2>{}) : run(Int<2>{}, Int<3>{});
+    else run(Int<1>{}, Int<2>{});
+  } else {
+    if (m.ng == 4) run(Int<4>{}, Int<4>{});
+    else if (KC > 1 || m.ng == 3) run(Int<3>{}, Int<4>{});
+    else if (m.ng == 2) run(Int<2>{}, Int<4>{});
+    else run(Int<1>{}, Int<4>{});
+  }
+}
+
+// NG: the groups of four regions the model has, where a kernel of its own for
+// them pays (one alpha per region on several chunks: 3 % over two loops in one
+// kernel, which spill more around them); 0: chosen in the kernel.
+template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0>
 __global__ __launch_bounds__(W * 64)
 __attribute__((amdgpu_waves_per_eu(OCC, OCC))) void k_mixed(DevModel m, Work w, Chunks cp,
                                                     int G, int nb) {
-  mixed_body<W, KC, PROJ, OCC, AM>(m, w, cp, G, nb, blockIdx.x);
+  mixed_body<W, KC, PROJ, OCC, AM, NG>(m, w, cp, G, nb, blockIdx.x);
 }
 
 // The group of workgroup blockIdx.x in launch `which` (0 likelihood, 1 row
@@ -1260,8 +1360,16 @@ hipError_t mixed_wa(const DevModel& m, const Work& w, const Chunks& cp, int G, i
           if (occ == 3)
             return go_mixed(k_mixed<W, 1, true, 3, AM>, nb, lds, s, m, w, cp, G, th);
         return go_mixed(k_mixed<W, 1, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
-      case 2: return go_mixed(k_mixed<W, 2, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
-      case 3: return go_mixed(k_mixed<W, 3, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
+      case 2:
+        if constexpr (AM == 1)
+          return m.ng == 4 ? go_mixed(k_mixed<W, 2, true, 2, 1, 4>, nb, lds, s, m, w, cp, G, th)
+                           : go_mixed(k_mixed<W, 2, true, 2, 1, 3>, nb, lds, s, m, w, cp, G, th);
+        return go_mixed(k_mixed<W, 2, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
+      case 3:
+        if constexpr (AM == 1)
+          return m.ng == 4 ? go_mixed(k_mixed<W, 3, true, 2, 1, 4>, nb, lds, s, m, w, cp, G, th)
+                           : go_mixed(k_mixed<W, 3, true, 2, 1, 3>, nb, lds, s, m, w, cp, G, th);
+        return go_mixed(k_mixed<W, 3, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
       default: return hipErrorInvalidValue;
     }
   }
