@@ -987,9 +987,31 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
 #pragma unroll
         for (int k = 0; k < NQB; ++k) Ak[k] = kf[(k * TR + tt) * 64 + lane];
         f64x4 a = {};
+        // projected rows: tile tt > 0 has R's rows 16 tt - 1 .., zero below the
+        // 16-region group tt but for one entry, region 16 tt - 1 of its first
+        // row, done in FP64 (region 4 (4 tt - 1) + 3: lane group 3; the row:
+        // register 0 of group 0)
+        double rl = 0.0, pl = 0.0;
+        if constexpr (!PROJ) {
 #pragma unroll
-        for (int k = 0; k < NQB; ++k)
-          a = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Ak[k], Bp[k], a, 0, 0, 0);
+          for (int k = 0; k < NQB; ++k)
+            a = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Ak[k], Bp[k], a, 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int it = 0; it < NU; ++it) {
+            if (it < tt) continue;                 // uniform
+#pragma unroll
+            for (int k = 4 * it; k < (4 * it + 4 < NQB ? 4 * it + 4 : NQB); ++k)
+              a = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Ak[k], Bp[k], a, 0, 0, 0);
+          }
+        }
+        if (PROJ && tt > 0) {
+          rl = (double)kf[((4 * tt - 1) * TR + tt) * 64 + 48];
+#pragma unroll
+          for (int it = 1; it < NU; ++it)
+            if (it == tt) pl = Bp[4 * it - 1];
+          pl = rl * __shfl(pl, 48 + (lane & 15));
+        }
         const double* Dt = Df + tt * 16;
         double r[4];
         if constexpr (PROJ) {
@@ -1001,9 +1023,16 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
             const bool mean_row = tt == 0 && g == 0 && j == 0;
             const double tgt = mean_row ? fma(-m.sqrtT, c, Dt[0]) : Dt[4 * j];
             r[j] = tgt - a[j];
+            if (j == 0) r[j] = g == 0 ? r[j] - pl : r[j];
             if (j & 1) chi_b = fma(r[j], r[j], chi_b);
             else chi_a = fma(r[j], r[j], chi_a);
             if (mean_row) rho = m.sqrtT * r[j];   // sum_t r = sqrt(T) e_0
+          }
+          if (tt > 0) {
+            const double e0 = __shfl(r[0], lane & 15);
+#pragma unroll
+            for (int it = 1; it < NU; ++it)
+              if (it == tt) u[it - 1][3] = fma(g == 3 ? rl : 0.0, e0, u[it - 1][3]);
           }
         } else {
           const bool ragged = (tt == TR - 1) && (m.T & 15);
@@ -1021,6 +1050,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
         }
 #pragma unroll
         for (int it = 0; it < NU; ++it) {
+          if (PROJ && it < tt) continue;
           const int q = 4 * it + qsub;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -1084,54 +1114,62 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
   }
 }
 
-// Sum the chunk partials of every (slot, row) in chunk order into the
-// first chunk's slab; one thread per (slot, row).
-__global__ __launch_bounds__(256) void k_grad_reduce(Work w, int S, int chunks) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)S * w.Bpad) return;
-  const size_t cs = (size_t)S * w.Bpad;
-  double acc = 0.0;
-  for (int c = 0; c < chunks; ++c) acc += w.gpart[c * cs + idx];
-  w.gpart[idx] = acc;
-}
+// lnL and the gradient rows from the chunk partials.  A workgroup takes
+// kGradRows rows: its threads add the chunks' partials of every (slot, row), in
+// chunk order, reading runs of kGradRows rows, into LDS; then form the rows'
+// entries there, and write them as one contiguous run.  (One thread per row
+// wrote entries a whole row apart: 25.8 us at 8192 rows of 36 entries, after
+// 9.0 us for the sums in a kernel of their own; MEASURED us in this one, which
+// reads 45 MB of partials.)  Invalid rows get -inf and a NaN gradient.
+constexpr int kGradRows = 16;
 
-// lnL and the gradient row from the reduced sums, one thread per row.
-// Invalid rows get -inf and a NaN gradient.
-__global__ __launch_bounds__(256) void k_grad_finalize(DevModel m, Work w, double chi0,
+__global__ __launch_bounds__(256) void k_grad_finalize(DevModel m, Work w, int S, int chunks,
+                                                       double chi0,
                                                        const double* __restrict__ theta,
                                                        double* __restrict__ out,
                                                        double* __restrict__ grad) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= w.B) return;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* s_sum = reinterpret_cast<double*>(smem);                 // [S][kGradRows]
+  double* s_gr = s_sum + (size_t)S * kGradRows;                    // [kGradRows][P]
   const int P = m.P, N = m.N, NB = m.NB, NA = m.NA;
-  const double* gp = w.gpart + b;
-  double* gr = grad + (size_t)b * P;
-  const RowParams rp = w.rows[b];
-  if (!rp.valid) {
-    out[b] = -INFINITY;
-    for (int k = 0; k < P; ++k) gr[k] = NAN;
-    return;
+  const int b0 = blockIdx.x * kGradRows, bl = threadIdx.x % kGradRows;
+  const int nrow = min(kGradRows, w.B - b0);
+  const size_t cs = (size_t)S * w.Bpad;
+  for (int s = threadIdx.x / kGradRows; s < S; s += 256 / kGradRows) {
+    const double* gp = w.gpart + (size_t)s * w.Bpad + b0 + bl;      // b0 + bl < Bpad
+    double acc = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) acc += gp[c * cs];
+    s_sum[s * kGradRows + bl] = acc;
   }
-  auto sum = [&](int slot) { return gp[(size_t)slot * w.Bpad]; };
-  const double s2 = rp.sigma * rp.sigma;
-  const double chi = sum(0) + chi0;
-  const double nFT = (double)m.F * (double)m.T;
-  out[b] = -0.5 * chi / s2 - 0.5 * nFT * log(2.0 * M_PI * s2);
-  for (int k = 0; k < P; ++k) gr[k] = 0.0;
-  const double kb = M_LN2 / s2;             // d/d beta: -ln(nu/nu_ref) = ln2 nl2
-  for (int r = 0; r < N; ++r) {
-    const int ia = r / NB, jb = r - ia * NB;
-    gr[jb] += kb * sum(4 + r);
-    if (NA > 0) gr[NB + ia] += sum(4 + N + r);
+  __syncthreads();
+  if (bl < nrow) {
+    const int b = b0 + bl;
+    const RowParams rp = w.rows[b];
+    const double s2 = rp.sigma * rp.sigma, kb = M_LN2 / s2;   // -ln(nu/nu_ref) = ln2 nl2
+    const double chi = s_sum[bl] + chi0, nFT = (double)m.F * (double)m.T;
+    auto sum = [&](int slot) { return s_sum[slot * kGradRows + bl]; };
+    for (int k = threadIdx.x / kGradRows; k < P; k += 256 / kGradRows) {
+      double v = 0.0;
+      if (k < NB) {
+        for (int i = 0; i < (NA > 0 ? NA : 1); ++i) v += kb * sum(4 + i * NB + k);
+      } else if (k < NB + NA) {
+        for (int j = 0; j < NB; ++j) v += sum(4 + N + (k - NB) * NB + j);
+        v = v / (theta[(size_t)b * P + k] * s2);
+      } else if (k == P - 1) {
+        v = chi / (s2 * rp.sigma) - nFT / rp.sigma;
+        out[b] = rp.valid ? -0.5 * chi / s2 - 0.5 * nFT * log(2.0 * M_PI * s2) : -INFINITY;
+      } else {
+        const double iw = rp.inv_w;
+        v = k == P - 4   ? sum(1) / s2
+            : k == P - 3 ? rp.A * iw * iw * sum(2) / s2
+                         : rp.A * iw * iw * iw * sum(3) / s2;
+      }
+      s_gr[bl * P + k] = rp.valid ? v : NAN;
+    }
   }
-  for (int i = 0; i < NA; ++i) gr[NB + i] = gr[NB + i] / (theta[(size_t)b * P + NB + i] * s2);
-  if (!(m.flags & 1u)) {
-    const double iw = rp.inv_w;
-    gr[P - 4] = sum(1) / s2;
-    gr[P - 3] = rp.A * iw * iw * sum(2) / s2;
-    gr[P - 2] = rp.A * iw * iw * iw * sum(3) / s2;
-  }
-  gr[P - 1] = chi / (s2 * rp.sigma) - nFT / rp.sigma;
+  __syncthreads();
+  for (int k = threadIdx.x; k < nrow * P; k += 256) grad[(size_t)b0 * P + k] = s_gr[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -1622,15 +1660,10 @@ hipError_t launch_grad_finalize(const DevModel& m, const Work& w, const GradShap
                                 const double* theta, double* out, double* grad,
                                 hipStream_t s) {
   const int S = grad_slots(m);
-  const size_t n = (size_t)S * w.Bpad;
-  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, S,
-                     g.chunks);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int blocks = (w.B + 255) / 256;
+  const int lds = kGradRows * (S + m.P) * 8;        // at most 50 KB (260 slots, 132 entries)
   const double chi0 = m.proj ? m.chi0 : 0.0;
-  hipLaunchKernelGGL(k_grad_finalize, dim3(blocks), dim3(256), 0, s, m, w, chi0, theta, out,
-                     grad);
+  hipLaunchKernelGGL(k_grad_finalize, dim3((w.B + kGradRows - 1) / kGradRows), dim3(256), lds, s,
+                     m, w, S, g.chunks, chi0, theta, out, grad);
   return hipGetLastError();
 }
 
