@@ -279,6 +279,9 @@ struct GroupDesc {
 // K times the residual).
 __host__ __device__ inline int grad_slots(const DevModel& m) { return 4 + m.N * (m.NA > 0 ? 2 : 1); }
 
+// Values of one region quad's row of 16-row tiles in the gradient kernel's LDS.
+__host__ __device__ inline int grad_kstride(int tiles) { return tiles * 64 + 4; }
+
 // Launch shape of the gradient kernel for B rows: 4-wave workgroups of 64
 // rows, `chunks` channel chunks of `per` channels, staged `fs` at a time.
 struct GradShape {

@@ -901,6 +901,13 @@ __global__ __launch_bounds__(256) void k_thin64_multi(const GroupDesc* __restric
 // workgroup owns 64 rows for a chunk of channels, restaging K and D every
 // `fs` channels, and writes one set of partial sums per (chunk, row).
 
+// Bound by the FP64 matrix instructions (46 ns each) and the vector and LDS work
+// that has to hide under them.  At 32 regions, 301 channels, 8192 rows, projected
+// (whole call): 408 us with both contractions over all of R and eight-way LDS
+// conflicts in the transposed read, 338 with R's zero groups left out (24
+// products of 32 a tile column) and the sums finished in one kernel, 255 with
+// the conflicts gone; 64 regions, 4096 rows: 918, 452.
+//
 // Register budgets that compile without spills: three waves per SIMD up to
 // 32 regions without amplitude masks, two up to 64 (48 with masks), else
 // what the variant needs.
@@ -921,7 +928,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
   map_block(nb, nc, bt, ch);
   const int TR = PROJ ? m.RT16 : m.TT16;    // 16-row tiles of the matrix
   const int N = m.N;
-  const int kdl = NQB * TR * 64;            // operand values per channel
+  const int ks = grad_kstride(TR), kdl = NQB * ks;   // operand values per quad row, per channel
   const int drow = PROJ ? m.RT16 * 16 : m.TT * 32;   // targets per channel
   double* s_t64 = reinterpret_cast<double*>(smem);                  // [64] 2^(m/64)
   AT* s_k = reinterpret_cast<AT*>(smem + 512);
@@ -951,11 +958,26 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
   // region 16 it + (lane & 15), read from the forward layout
   const int qsub = (lane & 15) >> 2;
   const int tsub = g + 16 * (lane & 3);
+  // The transposed read's 64 lanes take 4 rows of 4 regions of 4 quads: in the
+  // plain layout (regions 16 values apart, quad rows a multiple of 64) eight
+  // distinct FP64 banks.  Quad rows 4 values longer and regions 2 and 3 of a quad
+  // with their rows r at r ^ 2 give every half wave 32 distinct banks, and leave
+  // the forward read (a wave's 64 consecutive values) conflict-free.  (FP32
+  // operands need the longer rows only.)
+  const int swz = PROJ ? (lane >> 4) & 2 : 0, tswz = PROJ ? lane & 2 : 0;
   const int c0 = ch * per, c1 = min(m.F, c0 + per);
   for (int cs = c0; cs < c1; cs += fs) {
     const int fn = min(fs, c1 - cs);
     __syncthreads();                        // the previous stage is consumed
-    stage(s_k, kg + (size_t)cs * kdl, fn * kdl * (int)sizeof(AT));
+    // a wave copies a quad row (all tiles of one region quad); in FP64 the regions
+    // 2 and 3 of a quad exchange pairs of matrix rows on the way, see `swz`
+    for (int row = wave; row < fn * NQB; row += W) {
+      const uint4* src = reinterpret_cast<const uint4*>(kg + ((size_t)cs * NQB + row) * TR * 64);
+      uint4* dst = reinterpret_cast<uint4*>(s_k + (size_t)row * ks);
+      for (int k = lane; k < TR * 4 * (int)sizeof(AT); k += 64) {
+        dst[PROJ ? k ^ ((k >> 4) & 1) : k] = src[k];
+      }
+    }
     stage(s_D, dg + (size_t)cs * drow, fn * drow * 8);
     __syncthreads();
     for (int f = 0; f < fn; ++f) {
@@ -985,7 +1007,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
       for (int tt = 0; tt < TL; ++tt) {
         AT Ak[NQB];
 #pragma unroll
-        for (int k = 0; k < NQB; ++k) Ak[k] = kf[(k * TR + tt) * 64 + lane];
+        for (int k = 0; k < NQB; ++k) Ak[k] = kf[k * ks + tt * 64 + (lane ^ swz)];
         f64x4 a = {};
         // projected rows: tile tt > 0 has R's rows 16 tt - 1 .., zero below the
         // 16-region group tt but for one entry, region 16 tt - 1 of its first
@@ -1006,7 +1028,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
           }
         }
         if (PROJ && tt > 0) {
-          rl = (double)kf[((4 * tt - 1) * TR + tt) * 64 + 48];
+          rl = (double)kf[(4 * tt - 1) * ks + tt * 64 + (48 ^ 2)];
 #pragma unroll
           for (int it = 1; it < NU; ++it)
             if (it == tt) pl = Bp[4 * it - 1];
@@ -1054,7 +1076,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
           const int q = 4 * it + qsub;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const double at = q < NQB ? (double)kf[(q * TR + tt) * 64 + 4 * j + tsub] : 0.0;
+            const double at = q < NQB ? (double)kf[q * ks + tt * 64 + ((4 * j + tsub) ^ tswz)] : 0.0;
             u[it] = __builtin_amdgcn_mfma_f64_16x16x4f64(at, r[j], u[it], 0, 0, 0);
           }
         }
@@ -1062,7 +1084,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
       if (peel && g == 3) {
         // row N: target z_{N-1}; the entry is read from the forward layout
         // (tile TR - 1, lane 16 * 3: row 16 (TR - 1), region 4 (NQB - 1) + 3)
-        const double rl = (double)kf[((NQB - 1) * TR + TR - 1) * 64 + 48];
+        const double rl = (double)kf[(NQB - 1) * ks + (TR - 1) * 64 + (48 ^ 2)];
         const double e = s_D[(size_t)f * drow + N] - rl * Bp[NQB - 1];
         chi_a = fma(e, e, chi_a);
         u[NU - 1][3] = fma(rl, e, u[NU - 1][3]);
@@ -1119,7 +1141,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
 // chunk order, reading runs of kGradRows rows, into LDS; then form the rows'
 // entries there, and write them as one contiguous run.  (One thread per row
 // wrote entries a whole row apart: 25.8 us at 8192 rows of 36 entries, after
-// 9.0 us for the sums in a kernel of their own; MEASURED us in this one, which
+// 9.0 us for the sums in a kernel of their own; 11.9 us in this one, which
 // reads 45 MB of partials.)  Invalid rows get -inf and a NaN gradient.
 constexpr int kGradRows = 16;
 

@@ -109,8 +109,8 @@ constexpr int kGradChunk = 16;
 GradShape grad_shape(const DevModel& m, int Bpad) {
   GradShape g;
   g.nb = Bpad / 64;
-  const int per_ch = m.proj ? m.NQ * m.RT16 * 64 * 8 + m.RT16 * 16 * 8
-                           : m.NQ * m.TT16 * 64 * 4 + m.TT * 32 * 8;
+  const int per_ch = m.proj ? m.NQ * grad_kstride(m.RT16) * 8 + m.RT16 * 16 * 8
+                           : m.NQ * grad_kstride(m.TT16) * 4 + m.TT * 32 * 8;
   g.per = std::min(m.F, kGradChunk);
   g.chunks = (m.F + g.per - 1) / g.per;
   // stages of <= 40 KB with the power table (four workgroups per CU)
