@@ -32,6 +32,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <vector>
 
@@ -52,6 +53,7 @@ struct SkyDev {
   const double* lr;      // [F] log2(nu / nu0)
   const float4* beam4;   // [ceil(F / 4)][nlat][nlon]: channels 4 b .. 4 b + 3 of a
                          // pixel side by side (zero past the last channel)
+  const uint8_t* seen;   // [nlat][nlon] some channel's beam is non-zero, antenna frame
 };
 
 int pad_to(int n, int m) { return (n + m - 1) / m * m; }
@@ -351,6 +353,113 @@ __global__ __launch_bounds__(256) void k_beam_interleave(const float* __restrict
   }
   out[i] = make_float4(v[0], v[1], v[2], v[3]);
 }
+
+// seen[p] = whether any channel's beam is non-zero at antenna pixel p.
+__global__ __launch_bounds__(256) void k_beam_seen(const float4* __restrict__ beam4, int nb,
+                                                   size_t np, uint8_t* __restrict__ seen) {
+  const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= np) return;
+  bool any = false;
+  for (int b = 0; b < nb; ++b) {
+    const float4 v = beam4[(size_t)b * np + p];
+    any |= v.x != 0.f || v.y != 0.f || v.z != 0.f || v.w != 0.f;
+  }
+  seen[p] = any ? 1 : 0;
+}
+
+// The columns of a ring grouped by region (ascending column within one), one
+// workgroup per ring: region j holds e_j <= beta < e_{j+1}, the last closed, and
+// each region's run is padded to a multiple of four with weight-zero entries.
+// Columns whose pixel no step sees through a non-zero beam are left out (their
+// terms are zero; about two fifths of the benchmark sky's, which take k_sky_k
+// from 560 to 430 us).  Bound by the latency of a ring's few passes; 29 us on that
+// sky (92 with a thread per region walking the columns), against 1.6 ms of
+// sorting and 0.2 ms of uploads by the host.  seg: the runs'
+// starts; order, asort: columns and weights omega t_ex, in rows of L entries;
+// longest: the longest slice of a region group with every column counted.
+__global__ __launch_bounds__(256) void k_sky_regions(SkyDev s, const double* __restrict__ edges,
+                                                     int N, const int* __restrict__ shifts, int T,
+                                                     int L, int* __restrict__ seg,
+                                                     int* __restrict__ order,
+                                                     double* __restrict__ asort,
+                                                     int* __restrict__ longest) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int ring = blockIdx.x, tid = threadIdx.x, nlon = s.nlon;
+  int* s_reg = reinterpret_cast<int*>(smem);        // [nlon] region, -1 none or unseen
+  int* s_cnt = s_reg + nlon;                        // [N] seen columns, then the runs' fill
+  int* s_all = s_cnt + N;                           // [N] all columns
+  uint8_t* s_seen = reinterpret_cast<uint8_t*>(s_all + N);   // [nlon] antenna columns
+  const size_t row = (size_t)ring * nlon;
+  for (int c = tid; c < nlon; c += 256) s_seen[c] = s.seen[row + c];
+  for (int j = tid; j < 2 * N; j += 256) s_cnt[j] = 0;   // and s_all
+  __syncthreads();
+  for (int c = tid; c < nlon; c += 256) {
+    const double b = s.beta[row + c];
+    int lo = 0, hi = N + 1;                         // first edge above b
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (edges[mid] > b) hi = mid;
+      else lo = mid + 1;
+    }
+    int j = lo - 1;
+    if (b == edges[N]) j = N - 1;
+    if (b < edges[0] || b > edges[N]) j = -1;
+    bool up = false;
+    for (int t = 0; t < T && !up; ++t) {
+      const int h = c - shifts[t];
+      up = s_seen[h < 0 ? h + nlon : h];
+    }
+    s_reg[c] = up ? j : -1;
+    if (j >= 0) {
+      if (up) atomicAdd(&s_cnt[j], 1);
+      atomicAdd(&s_all[j], 1);
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int at = 0;
+    for (int j = 0; j < N; ++j) {
+      const int n = (s_cnt[j] + 3) / 4 * 4;
+      s_cnt[j] = at;
+      seg[(size_t)ring * (N + 1) + j] = at;
+      at += n;
+    }
+    seg[(size_t)ring * (N + 1) + N] = at;
+  }
+  for (int j0 = tid * kRegionsPerGroup; j0 < N; j0 += 256 * kRegionsPerGroup) {
+    int n = 0;
+    for (int j = j0; j < min(N, j0 + kRegionsPerGroup); ++j) n += (s_all[j] + 3) / 4 * 4;
+    atomicMax(longest, n);
+  }
+  __syncthreads();
+  // one wave places the columns, 64 at a time in order: a lane's place in its
+  // region's run is the run's fill plus the lanes before it with the same region
+  if (tid >= 64) return;
+  const double omega = s.omega[ring];
+  const int bits = 32 - __clz(N);
+  const unsigned long long before = (1ull << tid) - 1;
+  for (int c0 = 0; c0 < nlon; c0 += 64) {
+    const int c = c0 + tid, j = c < nlon ? s_reg[c] : -1;
+    unsigned long long same = __ballot(j >= 0);
+    for (int k = 0; k < bits; ++k) {
+      const unsigned long long m = __ballot((j >> k) & 1);
+      same &= (j >> k) & 1 ? m : ~m;
+    }
+    if (j < 0) continue;
+    const int fill = s_cnt[j], at = fill + __popcll(same & before);
+    order[(size_t)ring * L + at] = c;
+    asort[(size_t)ring * L + at] = omega * s.t_ex[row + c];
+    if ((same & ~before) == (1ull << tid)) s_cnt[j] = at + 1;   // the region's last lane
+  }
+  // the runs' padding: up to the next start, a multiple of four
+  for (int j = tid; j < N; j += 64)
+    for (int k = s_cnt[j]; k & 3; ++k) {
+      order[(size_t)ring * L + k] = 0;
+      asort[(size_t)ring * L + k] = 0.0;
+    }
+}
+
+size_t regions_lds(int nlon, int N) { return ((size_t)nlon + 2 * N) * 4 + (nlon + 3) / 4 * 4; }
 
 // K[j][f][t] = sum over the work items of j's region group, in order, of the
 // items' partial sums (first[g] .. first[g + 1] - 1 are group g's items).
@@ -825,10 +934,33 @@ struct Sky {
   SkyDev d{};
   double nu0 = 0.0;
   hipStream_t stream = nullptr;
-  std::vector<double> h_beta;      // for the masks of a partition
-  std::vector<double> h_omega, h_tex;   // for the region-sorted pixel weights
-  double last_ms = 0.0;            // last k_sky_corr duration (chromatic)
+  double last_ms = 0.0;            // last k_sky_k duration (chromatic)
+  // One call at a time works on a sky: calls are synchronous, and they share its
+  // stream and these buffers, which grow to the largest call's and go with it.
+  std::mutex mu;
+  struct Buf {
+    void* p = nullptr;
+    size_t bytes = 0;
+  } bufs[12];
 };
+
+// Buffer `slot` of at least `bytes` (its former contents are lost when it grows).
+template <typename T>
+hipError_t sky_buf(Sky* sk, int slot, size_t bytes, T** out) {
+  Sky::Buf& b = sk->bufs[slot];
+  if (b.bytes < bytes) {
+    if (b.p) (void)hipFree(b.p);
+    b = Sky::Buf();
+    const hipError_t e = hipMalloc(&b.p, bytes);
+    if (e != hipSuccess) {
+      b.p = nullptr;
+      return e;
+    }
+    b.bytes = bytes;
+  }
+  *out = static_cast<T*>(b.p);
+  return hipSuccess;
+}
 
 template <typename KernelT>
 hipError_t set_lds(KernelT k) {
@@ -843,7 +975,7 @@ int run_corr(Sky* sk, const int* d_shifts, int T, int smax, int Lz, double* d_ou
   const int chunks = (d.nlat + kRingChunk - 1) / kRingChunk;
   const size_t n = (size_t)d.F * T;
   double* part = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&part), n * chunks * 8);
+  hipError_t e = sky_buf(sk, 4, n * chunks * 8, &part);
   if (e != hipSuccess) return hip_err(e, "allocating partial sums");
   // two lanes per step: up to 128 steps per launch in up to 256 lanes
   const int tb = std::min(256, (2 * T + 63) / 64 * 64), TS = tb / 2;
@@ -861,7 +993,6 @@ int run_corr(Sky* sk, const int* d_shifts, int T, int smax, int Lz, double* d_ou
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(sk->stream);
-  (void)hipFree(part);
   return e == hipSuccess ? FGL_OK : hip_err(e, "normaliser kernels");
 }
 
@@ -886,25 +1017,20 @@ int run_lag(Sky* sk, const Lag& p, const int32_t* shifts, int T, double* importa
   std::partial_sum(h_start, h_start + NL + 1, h_start);
   std::vector<int> at(h_start, h_start + NL);
   for (int t = 0; t < T; ++t) h_steps[at[shifts[t] / p.g]++] = t;
-  struct Bufs {
-    void* p[8] = {};
-    ~Bufs() {
-      for (void* q : p)
-        if (q) (void)hipFree(q);
-    }
-  } m;
-  const size_t need[8] = {(size_t)d.nlat * NBk * sizeof(int2), (size_t)d.nlat * sizeof(int),
-                          (size_t)d.nlat * NT * sizeof(int2), (size_t)d.nlat * (NBk + 1) * sizeof(int),
-                          std::max(nw * chunks, np * nch) * 8, 2 * nw * 8, np * 8,
-                          h.size() * sizeof(int)};
-  hipError_t e = hipSuccess;
-  for (int k = 0; k < 8 && e == hipSuccess; ++k) e = hipMalloc(&m.p[k], need[k]);
+  int2 *blist = nullptr, *tasks = nullptr;
+  int *bcount = nullptr, *tstart = nullptr, *bad = nullptr;
+  double *part = nullptr, *Z = nullptr, *imp = nullptr;
+  hipError_t e = sky_buf(sk, 0, (size_t)d.nlat * NBk * sizeof(int2), &blist);
+  if (e == hipSuccess) e = sky_buf(sk, 1, (size_t)d.nlat * sizeof(int), &bcount);
+  if (e == hipSuccess) e = sky_buf(sk, 2, (size_t)d.nlat * NT * sizeof(int2), &tasks);
+  if (e == hipSuccess) e = sky_buf(sk, 3, (size_t)d.nlat * (NBk + 1) * sizeof(int), &tstart);
+  if (e == hipSuccess) e = sky_buf(sk, 4, std::max(nw * chunks, np * nch) * 8, &part);
+  if (e == hipSuccess) e = sky_buf(sk, 5, 2 * nw * 8, &Z);
+  if (e == hipSuccess) e = sky_buf(sk, 6, np * 8, &imp);
+  if (e == hipSuccess) e = sky_buf(sk, 7, h.size() * sizeof(int), &bad);
   if (e != hipSuccess) return hip_err(e, "allocating importance buffers");
-  int2 *blist = static_cast<int2*>(m.p[0]), *tasks = static_cast<int2*>(m.p[2]);
-  int *bcount = static_cast<int*>(m.p[1]), *tstart = static_cast<int*>(m.p[3]);
-  double *part = static_cast<double*>(m.p[4]), *Z = static_cast<double*>(m.p[5]), *W = Z + nw;
-  double* imp = static_cast<double*>(m.p[6]);
-  int *bad = static_cast<int*>(m.p[7]), *start = bad + 1, *steps = start + NL + 1;
+  double* W = Z + nw;
+  int *start = bad + 1, *steps = start + NL + 1;
   hipStream_t st = sk->stream;
   if ((e = set_lds(k_lag_corr<MODE>)) == hipSuccess) e = set_lds(k_lag_imp<MODE>);
   if (e == hipSuccess)
@@ -957,8 +1083,7 @@ int run_k(Sky* sk, const int* d_shifts, int T, int smax, const int* d_order,
   // two lanes per step: T steps per launch in up to 256 lanes
   const int tb = std::min(256, (2 * T + 63) / 64 * 64), TS = tb / 2;  const size_t ft = (size_t)d.F * T;
   double* part = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&part),
-                           (size_t)n_items * kRegionsPerGroup * ft * 8);
+  hipError_t e = sky_buf(sk, 4, (size_t)n_items * kRegionsPerGroup * ft * 8, &part);
   if (e != hipSuccess) return hip_err(e, "allocating partial sums");
   const size_t lds = k_lds(d.nlon, smax, Lg);
   const dim3 grid((d.F + 3) / 4, n_items);
@@ -986,7 +1111,6 @@ int run_k(Sky* sk, const int* d_shifts, int T, int smax, const int* d_order,
   if (ms && e == hipSuccess) (void)hipEventElapsedTime(ms, e0, e1);
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
-  (void)hipFree(part);
   return e == hipSuccess ? FGL_OK : hip_err(e, "K kernels");
 }
 
@@ -1051,9 +1175,11 @@ int to_device(T** dst, const T* src, size_t count, const char* what) {
 
 void free_sky(Sky* sk) {
   const void* ps[] = {sk->d.omega, sk->d.t_ex, sk->d.beta, sk->d.beam, sk->d.hor, sk->d.lr,
-                      sk->d.beam4};
+                      sk->d.beam4, sk->d.seen};
   for (const void* p : ps)
     if (p) (void)hipFree(const_cast<void*>(p));
+  for (const Sky::Buf& b : sk->bufs)
+    if (b.p) (void)hipFree(b.p);
   if (sk->stream) (void)hipStreamDestroy(sk->stream);
   delete sk;
 }
@@ -1167,9 +1293,6 @@ int fgl_sky_create(int nlat, int nlon, int F, const double* omega, const double*
   sk->d.nlon = nlon;
   sk->d.F = F;
   sk->d.t_cmb = t_cmb;
-  sk->h_beta.assign(beta, beta + np);
-  sk->h_omega.assign(omega, omega + nlat);
-  sk->h_tex.assign(t_ex, t_ex + np);
   double *om = nullptr, *tx = nullptr, *bt = nullptr, *l2 = nullptr;
   float* bm = nullptr;
   uint8_t* hz = nullptr;
@@ -1198,10 +1321,17 @@ int fgl_sky_create(int nlat, int nlon, int F, const double* omega, const double*
   // the beam interleaved by four channels for the K kernel
   const size_t n4 = (size_t)((F + 3) / 4) * np;
   float4* b4 = nullptr;
+  uint8_t* seen = nullptr;
   if ((e = hipMalloc(reinterpret_cast<void**>(&b4), n4 * sizeof(float4))) == hipSuccess) {
     sk->d.beam4 = b4;
+    e = hipMalloc(reinterpret_cast<void**>(&seen), np);
+  }
+  if (e == hipSuccess) {
+    sk->d.seen = seen;
     hipLaunchKernelGGL(k_beam_interleave, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0,
                        sk->stream, bm, F, np, n4, b4);
+    hipLaunchKernelGGL(k_beam_seen, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, sk->stream,
+                       b4, (F + 3) / 4, np, seen);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(sk->stream);
   }
@@ -1230,6 +1360,7 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
   const bool on_grid = imp_lds <= 160 * 1024 && lag_plan(shifts, T, sk->d.nlon, &lag);
   hipError_t e = hipSetDevice(sk->dev);
   if (e != hipSuccess) return hip_err(e, "hipSetDevice");
+  std::lock_guard<std::mutex> lk(sk->mu);
   const SkyDev& d = sk->d;
   int* d_sh = nullptr;
   double *Z = nullptr, *imp = nullptr;
@@ -1237,11 +1368,13 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
     return scheme == FGL_WEIGHT_BEAM ? run_lag<kCorrBeam>(sk, lag, shifts, T, importance)
            : scheme == FGL_WEIGHT_SKY ? run_lag<kCorrSky>(sk, lag, shifts, T, importance)
                                       : run_lag<kCorrHorizon>(sk, lag, shifts, T, importance);
-  if ((rc = to_device(&d_sh, shifts, (size_t)T, "uploading shifts")) != FGL_OK) return rc;
-  if ((e = hipMalloc(reinterpret_cast<void**>(&Z), (size_t)d.F * T * 8)) != hipSuccess ||
-      (e = hipMalloc(reinterpret_cast<void**>(&imp), (size_t)d.nlat * d.nlon * 8)) != hipSuccess) {
-    rc = hip_err(e, "allocating importance buffers");
-  }
+  if ((e = sky_buf(sk, 7, (size_t)T * sizeof(int), &d_sh)) != hipSuccess ||
+      (e = sky_buf(sk, 5, (size_t)d.F * T * 8, &Z)) != hipSuccess ||
+      (e = sky_buf(sk, 6, (size_t)d.nlat * d.nlon * 8, &imp)) != hipSuccess)
+    return hip_err(e, "allocating importance buffers");
+  if ((e = hipMemcpyAsync(d_sh, shifts, (size_t)T * sizeof(int), hipMemcpyHostToDevice,
+                          sk->stream)) != hipSuccess)
+    return hip_err(e, "uploading shifts");
   if (rc == FGL_OK) {
     rc = scheme == FGL_WEIGHT_BEAM ? run_corr<kCorrBeam>(sk, d_sh, T, smax, Lz, Z)
          : scheme == FGL_WEIGHT_SKY ? run_corr<kCorrSky>(sk, d_sh, T, smax, Lz, Z)
@@ -1267,7 +1400,7 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
     double* part = nullptr;
     if (imp_lds > 160 * 1024) {
       rc = set_err(FGL_EINVAL, "T=%d and nlon=%d do not fit one workgroup's LDS", T, d.nlon);
-    } else if ((e = hipMalloc(reinterpret_cast<void**>(&part), np * nch * 8)) != hipSuccess) {
+    } else if ((e = sky_buf(sk, 4, np * nch * 8, &part)) != hipSuccess) {
       rc = hip_err(e, "allocating importance partials");
     } else {
       auto launch = [&](auto kern) {
@@ -1289,11 +1422,7 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
       if (e == hipSuccess) e = hipMemcpy(importance, imp, np * 8, hipMemcpyDeviceToHost);
       if (e != hipSuccess) rc = hip_err(e, "importance kernel");
     }
-    if (part) (void)hipFree(part);
   }
-  if (d_sh) (void)hipFree(d_sh);
-  if (Z) (void)hipFree(Z);
-  if (imp) (void)hipFree(imp);
   return rc;
 }
 
@@ -1322,81 +1451,64 @@ int fgl_sky_chromatic(fgl_sky* sh, const double* edges, int n_regions, const int
   if (rc != FGL_OK) return rc;
   hipError_t e = hipSetDevice(sk->dev);
   if (e != hipSuccess) return hip_err(e, "hipSetDevice");
+  std::lock_guard<std::mutex> lk(sk->mu);
   const SkyDev& d = sk->d;
-  const int N = n_regions, nlon = d.nlon;
-  // masks: region j holds e_j <= beta < e_{j+1}, the last closed; then the
-  // columns of each ring grouped by region (ascending column within one),
-  // every region's run padded to a multiple of four with weight-zero entries
-  std::vector<int> regs((size_t)d.nlat * nlon), counts((size_t)d.nlat * N, 0);
-  int L = 8;
-  for (int r = 0; r < d.nlat; ++r) {
-    int len = 0;
-    for (int c = 0; c < nlon; ++c) {
-      const double b = sk->h_beta[(size_t)r * nlon + c];
-      int j = (int)(std::upper_bound(edges, edges + N + 1, b) - edges) - 1;
-      if (b == edges[N]) j = N - 1;
-      if (b < edges[0] || b > edges[N]) j = -1;
-      regs[(size_t)r * nlon + c] = j;
-      if (j >= 0) ++counts[(size_t)r * N + j];
-    }
-    for (int j = 0; j < N; ++j) len += pad4(counts[(size_t)r * N + j]);
-    L = std::max(L, len);
-  }
+  const int N = n_regions, nlon = d.nlon, smax = *std::max_element(shifts, shifts + T);
+  if (k_lds(nlon, smax, 8) > 160 * 1024 || regions_lds(nlon, N) > 160 * 1024)
+    return set_err(FGL_EINVAL, "nlon=%d does not fit one workgroup's LDS", nlon);
+  // the columns of each ring grouped by region, on the device: runs padded to a
+  // multiple of four fit rows of L entries
+  const int L = std::max(8, pad4(nlon + 3 * std::min(N, nlon)));
+  const size_t nseg = (size_t)d.nlat * (N + 1);
+  int *d_sh = nullptr, *d_order = nullptr, *d_seg = nullptr, *d_first = nullptr;
+  double *d_edges = nullptr, *d_K = nullptr, *d_as = nullptr;
+  int4* d_items = nullptr;
+  if ((e = sky_buf(sk, 7, (size_t)T * sizeof(int), &d_sh)) != hipSuccess ||
+      (e = sky_buf(sk, 8, (size_t)(N + 1) * 8, &d_edges)) != hipSuccess ||
+      (e = sky_buf(sk, 0, (size_t)d.nlat * L * sizeof(int), &d_order)) != hipSuccess ||
+      (e = sky_buf(sk, 2, (size_t)d.nlat * L * 8, &d_as)) != hipSuccess ||
+      (e = sky_buf(sk, 1, (nseg + 1) * sizeof(int), &d_seg)) != hipSuccess ||
+      (e = sky_buf(sk, 9, (size_t)N * d.F * T * 8, &d_K)) != hipSuccess)
+    return hip_err(e, "allocating region buffers");
+  hipStream_t st = sk->stream;
+  const int zero = 0;
+  std::vector<int> seg(nseg + 1);                   // and the longest unfiltered slice
+  if ((e = set_lds(k_sky_regions)) != hipSuccess ||
+      (e = hipMemcpyAsync(d_sh, shifts, (size_t)T * sizeof(int), hipMemcpyHostToDevice, st)) != hipSuccess ||
+      (e = hipMemcpyAsync(d_edges, edges, (size_t)(N + 1) * 8, hipMemcpyHostToDevice, st)) != hipSuccess ||
+      (e = hipMemcpyAsync(d_seg + nseg, &zero, sizeof(int), hipMemcpyHostToDevice, st)) != hipSuccess)
+    return hip_err(e, "uploading regions");
+  hipLaunchKernelGGL(k_sky_regions, dim3(d.nlat), dim3(256), regions_lds(nlon, N), st, d, d_edges,
+                     N, d_sh, T, L, d_seg, d_order, d_as, d_seg + nseg);
+  if ((e = hipGetLastError()) != hipSuccess ||
+      (e = hipMemcpyAsync(seg.data(), d_seg, (nseg + 1) * sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+      (e = hipStreamSynchronize(st)) != hipSuccess)
+    return hip_err(e, "grouping pixels by region");
+  if (k_lds(nlon, smax, std::max(8, seg[nseg])) > 160 * 1024)
+    return set_err(FGL_EINVAL, "nlon=%d does not fit one workgroup's LDS", nlon);
   // longest slice of one region group's columns in a ring (a multiple of 4)
   int Lg = 8;
   for (int r = 0; r < d.nlat; ++r)
     for (int j0 = 0; j0 < N; j0 += kRegionsPerGroup) {
-      int len = 0;
-      for (int j = j0; j < std::min(N, j0 + kRegionsPerGroup); ++j)
-        len += pad4(counts[(size_t)r * N + j]);
-      Lg = std::max(Lg, len);
+      const int* sg = &seg[(size_t)r * (N + 1)];
+      Lg = std::max(Lg, sg[std::min(N, j0 + kRegionsPerGroup)] - sg[j0]);
     }
-  const int smax = *std::max_element(shifts, shifts + T);
-  if (k_lds(nlon, smax, Lg) > 160 * 1024)
-    return set_err(FGL_EINVAL, "nlon=%d does not fit one workgroup's LDS", nlon);
-  std::vector<int> order((size_t)d.nlat * L, 0), seg((size_t)d.nlat * (N + 1));
-  std::vector<double> asort((size_t)d.nlat * L, 0.0);
-  for (int r = 0; r < d.nlat; ++r) {
-    int* sg = &seg[(size_t)r * (N + 1)];
-    sg[0] = 0;
-    for (int j = 0; j < N; ++j) sg[j + 1] = sg[j] + pad4(counts[(size_t)r * N + j]);
-    std::vector<int> fill(sg, sg + N);
-    for (int c = 0; c < nlon; ++c) {
-      const int j = regs[(size_t)r * nlon + c];
-      if (j < 0) continue;
-      const size_t at = (size_t)r * L + fill[j]++;
-      order[at] = c;
-      asort[at] = sk->h_omega[r] * sk->h_tex[(size_t)r * nlon + c];
-    }
-  }
   std::vector<int4> items;
   std::vector<int> first;
   k_items(seg, d.nlat, N, items, first);
-  int *d_sh = nullptr, *d_order = nullptr, *d_seg = nullptr, *d_first = nullptr;
-  int4* d_items = nullptr;
-  double *d_K = nullptr, *d_as = nullptr;
-  if ((rc = to_device(&d_sh, shifts, (size_t)T, "uploading shifts")) == FGL_OK &&
-      (rc = to_device(&d_order, order.data(), order.size(), "uploading the region order")) == FGL_OK &&
-      (rc = to_device(&d_as, asort.data(), asort.size(), "uploading pixel weights")) == FGL_OK &&
-      (rc = to_device(&d_seg, seg.data(), seg.size(), "uploading region segments")) == FGL_OK &&
-      (rc = to_device(&d_items, items.data(), items.size(), "uploading work items")) == FGL_OK &&
-      (rc = to_device(&d_first, first.data(), first.size(), "uploading work items")) == FGL_OK) {
-    if ((e = hipMalloc(reinterpret_cast<void**>(&d_K), (size_t)N * d.F * T * 8)) != hipSuccess)
-      rc = hip_err(e, "allocating K");
-  }
+  if ((e = sky_buf(sk, 10, items.size() * sizeof(int4), &d_items)) != hipSuccess ||
+      (e = sky_buf(sk, 11, first.size() * sizeof(int), &d_first)) != hipSuccess ||
+      (e = hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice, st)) != hipSuccess ||
+      (e = hipMemcpyAsync(d_first, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice, st)) != hipSuccess)
+    return hip_err(e, "uploading work items");
   float ms = 0.0f;
-  if (rc == FGL_OK)
-    rc = run_k(sk, d_sh, T, smax, d_order, d_as, d_seg, N, L, Lg, d_items, (int)items.size(),
-               d_first, d_K, &ms);
-  if (rc == FGL_OK) {
-    sk->last_ms = ms;
-    if ((e = hipMemcpy(K, d_K, (size_t)N * d.F * T * 8, hipMemcpyDeviceToHost)) != hipSuccess)
-      rc = hip_err(e, "copy K");
-  }
-  const void* ps[] = {d_sh, d_order, d_seg, d_K, d_as, d_items, d_first};
-  for (const void* p : ps)
-    if (p) (void)hipFree(const_cast<void*>(p));
-  return rc;
+  rc = run_k(sk, d_sh, T, smax, d_order, d_as, d_seg, N, L, Lg, d_items, (int)items.size(),
+             d_first, d_K, &ms);
+  if (rc != FGL_OK) return rc;
+  sk->last_ms = ms;
+  if ((e = hipMemcpy(K, d_K, (size_t)N * d.F * T * 8, hipMemcpyDeviceToHost)) != hipSuccess)
+    return hip_err(e, "copy K");
+  return FGL_OK;
 }
 
 int fgl_sky_kernel_ms(const fgl_sky* sh, double* ms) {
