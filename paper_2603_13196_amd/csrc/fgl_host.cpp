@@ -694,11 +694,19 @@ Tile default_tile(Kind k, const DevModel& d, int B) {
 
 int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb, const double* d_theta,
             int B, double* d_out, hipStream_t s) {
+  // a small thin batch is one launch: the three below do their part or nothing
+  wb.w.thin_rows = thin_rows_of(k, m->dm, tile, B, d_theta, d_out);
+  wb.w.theta = d_theta;
+  wb.w.out = d_out;
   const int rc = enqueue_partials(m, k, tile, wb, d_theta, B, s);
-  if (rc != FGL_OK) return rc;
   hipError_t e;
-  if ((e = launch_finalize(k, m->dm, wb.w, tile, d_out, s)) != hipSuccess)
-    return hip_err(e, "finalize kernel");
+  if (rc != FGL_OK) {
+    wb.w.thin_rows = 0;
+    return rc;
+  }
+  e = launch_finalize(k, m->dm, wb.w, tile, d_out, s);
+  wb.w.thin_rows = 0;            // the workspace's other users launch all they need
+  if (e != hipSuccess) return hip_err(e, "finalize kernel");
   return FGL_OK;
 }
 
@@ -1177,6 +1185,14 @@ int fgl_loglike_batch(fgl_model* mh, const double* theta, int B, double* out, in
     tile = tile_for(m, k, B);
     if ((rc = ensure_work(m, wb, B, n_groups(m->dm, tile), true)) != FGL_OK) return rc;
     std::memcpy(wb.h_theta, theta, tb);
+  }
+  // a one-launch call reads its rows from the pinned staging and writes its
+  // results there: neither copies nor a graph
+  if (thin_rows_of(k, m->dm, tile, B, wb.h_theta, wb.h_out) > 0) {
+    if ((rc = enqueue(m, k, tile, wb, wb.h_theta, B, wb.h_out, s)) != FGL_OK) return rc;
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_err(e, "hipStreamSynchronize");
+    std::memcpy(out, wb.h_out, (size_t)B * 8);
+    return FGL_OK;
   }
   // graph replay for a (precision, B, tile) seen before; eager otherwise
   const GraphKey gk{k, B, tile.waves, tile.fc, tile.occ};

@@ -256,6 +256,11 @@ struct Work {
   double* partial;       // [ngroups][Bpad]
   int ngroup_cap;        // capacity of partial in groups
   double* gpart;         // gradient partials [chunks][grad_slots][Bpad]
+  // one-launch calls (thin_rows_of): rows per workgroup, 0 for the three
+  // launches, and the call's rows and results
+  int thin_rows = 0;
+  const double* theta = nullptr;
+  double* out = nullptr;
 };
 
 // One model's rows in a launch shared by several models whose likelihood
@@ -282,6 +287,11 @@ __host__ __device__ inline int grad_slots(const DevModel& m) { return 4 + m.N * 
 // Values of one region quad's row of 16-row tiles in the gradient kernel's LDS.
 __host__ __device__ inline int grad_kstride(int tiles) { return tiles * 64 + 4; }
 
+// Rows per workgroup of the one-launch thin kernel for B rows (theta to out), or
+// 0 where the three launches are taken.
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
+                 const double* out);
+size_t thin_rows_lds(const DevModel& m, int rows);
 // Launch shape of the gradient kernel for B rows: 4-wave workgroups of 64
 // rows, `chunks` channel chunks of `per` channels, staged `fs` at a time.
 struct GradShape {
