@@ -569,7 +569,7 @@ __global__ __launch_bounds__(256) void k_sky_importance(SkyDev s, const int* __r
 // normalisers and importance on a lag grid
 //
 // When the steps' shifts are multiples of g up to g (S - 1) with S not far from
-// the number of steps (evenly spaced steps), Z and I are Toeplitz products on
+// the number of steps (evenly spaced steps; lag_plan has the line), Z and I are Toeplitz products on
 // the columns of a residue class mod g: Z at lag s sums b[h] a[h + s], and
 // I sums b[q - s] / Z_s over s.  A lane takes 16 x 16 blocks of such a product
 // with the 31 diagonal values in registers, so an LDS value feeds about ten
@@ -900,11 +900,20 @@ size_t lag_imp_lds(const Lag& p) {
 }
 
 // The lag grid of a call's shifts, and whether it takes the call: at most 64
-// lag blocks (a wave holds them), the kernels' LDS, and at most four lags per
-// step (of at least 32).  Whole calls on the 256 x 512 sky, 301 channels, by the
-// gather kernels and on the grid (us): 96 steps over 96, 192, 288 and 384 lags
-// 1734 and 635, 1874 and 870, 1871 and 1266, 1954 and 1460; 24 steps over 128
-// lags 1377 and 659; 8 steps over 128 lags 718 and 668.
+// lag blocks (a wave holds them), the kernels' LDS, at most four lags per
+// step (of at least 32), and rings or steps enough to fill its waves (a ring's
+// blocks of 16 x 16 go over 64 lanes in whole passes, so narrow rings leave
+// lanes idle; the gather kernels' time goes with columns times steps).
+// Whole calls on the 256 x 512 sky, 301 channels, by the gather kernels and on
+// the grid (us): 96 steps over 96, 192, 288 and 384 lags 1734 and 635, 1874 and
+// 870, 1871 and 1266, 1954 and 1460; 24 steps over 128 lags 1377 and 659; 8
+// steps over 128 lags 718 and 668.  128 rings, 200 channels, evenly spaced
+// steps (buffers kept on both sides): 300 columns 5 steps 191 and 204, 16 184 and
+// 202, 60 242 and 207; 230 columns 153 and 180 at 16, 195 and 183 at 60; 200
+// columns 145 and 180 at 16, 185 and 185 at 60.  Wider rings: 59 x 364, 247
+// channels, 6 steps 186 and 163; 178 x 348, 21 channels, 27 steps 181 and 135;
+// 256 x 512, 301 channels, 8 steps 651 and 444.
+constexpr int kLagMinCols = 340, kLagMinWork = 12000;
 bool lag_plan(const int32_t* shifts, int T, int nlon, Lag* out) {
   Lag p{};
   int g = 0;
@@ -918,7 +927,8 @@ bool lag_plan(const int32_t* shifts, int T, int nlon, Lag* out) {
   p.HB = ((nlon + p.g - 1) / p.g + kLagBlock - 1) / kLagBlock;
   p.inv_g = p.g > 1 ? (unsigned)(((1ull << 32) + p.g - 1) / p.g) : 0u;
   *out = p;
-  return p.SB <= 64 && p.SB * kLagBlock <= 4 * pad_to(T, 32) && p.blocks() < 1 << 20 &&
+  return (nlon >= kLagMinCols || (long long)nlon * T >= kLagMinWork) && p.SB <= 64 &&
+         p.SB * kLagBlock <= 4 * pad_to(T, 32) && p.blocks() < 1 << 20 &&
          (size_t)p.blocks() + p.ext() <= 64 * 1024 && lag_corr_lds(p) <= 160 * 1024 &&
          lag_imp_lds(p) <= 160 * 1024;
 }

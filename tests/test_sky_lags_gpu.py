@@ -29,6 +29,11 @@ def _shifts(kind, nlon, T):
     ("5", 5, 128, 4, 96), ("7", 6, 50, 3, 8), ("21", 4, 512, 3, 4), ("near", 6, 120, 5, 20),
     ("scattered", 6, 40, 5, 24), ("scattered", 5, 512, 4, 6), ("zero", 4, 20, 3, 5),
     ("1", 4, 1, 2, 1), ("1", 3, 17, 1, 1),
+    # rings wide enough for the grid kernels whatever the steps, and the columns
+    # and columns times steps on both sides of that line
+    ("1", 5, 400, 9, 48), ("2", 4, 341, 6, 30), ("5", 5, 640, 4, 96), ("7", 6, 350, 3, 8),
+    ("near", 6, 420, 5, 20), ("scattered", 5, 400, 5, 24), ("zero", 4, 340, 3, 5),
+    ("1", 3, 357, 1, 1), ("3", 6, 339, 5, 17), ("2", 5, 240, 4, 50), ("2", 5, 240, 4, 49),
 ])
 def test_importance_over_shift_patterns(kind, nlat, nlon, F, T):
     fgl = lib()
