@@ -11,6 +11,7 @@
 namespace fgl {
 
 constexpr double kThinRowsOps = 2.0e8;   // one-launch calls: a few us of the vector units
+constexpr int kThinRowsMax = 2048;       // and eight rows or fewer for each CU
 
 int cols_per_wave(Kind k) { return k == kFP64 ? 16 : (k == kThin ? 64 : 32); }
 
@@ -82,22 +83,25 @@ size_t thin_rows_lds(const DevModel& m, int rows) {
 // kernel.  A channel's latency goes as c = 12 NT + T (NT + 30), 3.5 ns a unit and
 // four channels a turn, so the extra turns must cost less than 7 us:
 // (turns - 1) c <= 450.  Whole calls, three launches and one (us):
-//   N4 F151 T1 B1000 14.9, 7.8; B16384 23.6, 15.8     N32 F301 T1 B1000 20.0, 18.2
+//   N4 F151 T1 B1000 14.9, 7.8; B2000 15.4, 10.7     N32 F301 T1 B1000 20.0, 18.2
 //   N24 F200 T6 B300 21.0, 12.8     N16 F151 T20 B900 26.1, 18.5
-// A channel of more than c = 1650 (many bins) is slower from the caches even in
-// one turn, and above 240 channels (a line of data each) the 32 KB L1 holds only
-// for one workgroup per CU.
+// A channel of more than c = 1650 (many bins), or 1000 with eight rows, is slower
+// from the caches even in one turn, and past eight rows for each of the 256 CUs the staged kernel's rows
+// fill the chip too.
 //   past the line: N10 F301 T1 B3000 18.5, 19.5     N16 F151 T20 B1500 26.0, 32.5
 //   N4 F301 T8 B3000 17.0, 23.4     N8 F301 T40 B500 26.1, 33.5
-//   N4 F151 T64 B300 19.4, 25.4     N4 F301 T1 B9000 24.4, 37.8
+//   N4 F151 T64 B300 19.4, 25.4     N4 F151 T1 B6000 15.0, 19.0; B16384 23.6, 27.7
+//   N4 F120 T30 B2000 15.4, 16.0    N16 F120 T10 B2000 19.6, 12.7 (c 652, taken)
+//   N10 F151 T1 B6000 18.6, 18.4    N4 F100 T1 B6000 15.4, 14.2 (left out for one line)
 int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
                  const double* out) {
   if (k != kThin || t.group != 4) return 0;
   if ((double)B * m.F * (m.NT * m.T + 12 * m.NT + 2 * m.T) > kThinRowsOps) return 0;
-  const int rows = B <= 1024 ? 4 : B <= 2048 ? 8 : 16;
+  if (B > kThinRowsMax) return 0;
+  const int rows = B <= 1024 ? 4 : 8;
   const int64_t turns = ((m.F + 3) / 4 * rows + 255) / 256;
   const int64_t c = 12 * m.NT + m.T * (m.NT + 30);
-  if ((turns - 1) * c > 450 || c > 1650 || (m.F > 240 && B > rows * kCUs)) return 0;
+  if ((turns - 1) * c > 450 || c > (rows == 4 ? 1650 : 1000)) return 0;
   if (thin_rows_lds(m, rows) > 48 * 1024) return 0;
   // results over the rows they come from: every row is read before any is written
   // only by the three launches
