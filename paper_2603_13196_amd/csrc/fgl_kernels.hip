@@ -177,7 +177,7 @@ using Int = std::integral_constant<int, V>;
 // one chunk (the other forms find their last tile's at run time: the branch
 // costs them nothing, and compiled apart their loops spilled more).
 template <int KC, bool PROJ, int AM, int NG, int JQ>
-__device__ __forceinline__ void mixed_channels(const DevModel& m, const Work& w, int G, int f0,
+__device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork& w, int G, int f0,
                                                int fn, int b, const double* s_tab,
                                                const unsigned char* s_kd, const double* s_D) {
   constexpr int ND = PROJ ? kProjDigits : 4;       // digits of the matrix rows
@@ -513,7 +513,7 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const Work& w,
 // call it for one model (k_mixed) or for several that share the compiled
 // variant (k_mixed_multi).
 template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0>
-__device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, const Chunks& cp,
+__device__ __forceinline__ void mixed_body(const DevModel& m, const RowsWork& w, const Chunks& cp,
                                            int G, int nb, int block) {
   constexpr int ND = PROJ ? kProjDigits : 4;       // digits of the matrix rows
   extern __shared__ __align__(16) unsigned char smem[];
@@ -566,7 +566,7 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const Work& w, con
 // kernel, which spill more around them); 0: chosen in the kernel.
 template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0>
 __global__ __launch_bounds__(W * 64)
-__attribute__((amdgpu_waves_per_eu(OCC, OCC))) void k_mixed(DevModel m, Work w, Chunks cp,
+__attribute__((amdgpu_waves_per_eu(OCC, OCC))) void k_mixed(DevModel m, RowsWork w, Chunks cp,
                                                     int G, int nb) {
   mixed_body<W, KC, PROJ, OCC, AM, NG>(m, w, cp, G, nb, blockIdx.x);
 }
@@ -606,7 +606,7 @@ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) void k_mixed_multi(const GroupDes
 // FP32 row product, the peeled last row of R in FP64 from the FP32 power.
 
 template <int W, int NPB, bool AB, bool PROJ>
-__global__ __launch_bounds__(W * 64) void k_fp32(DevModel m, Work w, int fc, int G,
+__global__ __launch_bounds__(W * 64) void k_fp32(DevModel m, RowsWork w, int fc, int G,
                                                  int nb, int nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(W * 64) void k_fp32(DevModel m, Work w, int fc, int
 // row product.
 
 template <int W, int NQB, bool AB, bool PROJ>
-__global__ __launch_bounds__(W * 64) void k_fp64(DevModel m, Work w, int fc, int G,
+__global__ __launch_bounds__(W * 64) void k_fp64(DevModel m, RowsWork w, int fc, int G,
                                                  int nb, int nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   using AT = typename std::conditional<PROJ, double, float>::type;   // operand type
@@ -812,7 +812,7 @@ __global__ __launch_bounds__(W * 64) void k_fp64(DevModel m, Work w, int fc, int
 // reduction group, as the other kernels.
 
 template <int NT, bool AB>
-__device__ __forceinline__ void thin_body(const DevModel& m, const Work& w, int fc, int G,
+__device__ __forceinline__ void thin_body(const DevModel& m, const RowsWork& w, int fc, int G,
                                           int nb, int nc, int block) {
   extern __shared__ __align__(16) unsigned char smem[];
   int bt, ch;
@@ -864,7 +864,7 @@ __device__ __forceinline__ void thin_body(const DevModel& m, const Work& w, int 
 }
 
 template <int NT, bool AB>
-__global__ __launch_bounds__(256) void k_thin64(DevModel m, Work w, int fc, int G, int nb,
+__global__ __launch_bounds__(256) void k_thin64(DevModel m, RowsWork w, int fc, int G, int nb,
                                                 int nc) {
   thin_body<NT, AB>(m, w, fc, G, nb, nc, blockIdx.x);
 }
@@ -1048,7 +1048,7 @@ constexpr int grad_waves() {
 template <int W, int NQB, bool AB, bool PROJ>
 __global__ __launch_bounds__(W * 64)
 __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
-    DevModel m, Work w, int per, int fs, int nb, int nc) {
+    DevModel m, RowsWork w, int per, int fs, int nb, int nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   using AT = typename std::conditional<PROJ, double, float>::type;   // operand type
   constexpr int NU = (NQB + 3) / 4;         // 16-region output groups
@@ -1274,7 +1274,7 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
 // reads 45 MB of partials.)  Invalid rows get -inf and a NaN gradient.
 constexpr int kGradRows = 16;
 
-__global__ __launch_bounds__(256) void k_grad_finalize(DevModel m, Work w, int S, int chunks,
+__global__ __launch_bounds__(256) void k_grad_finalize(DevModel m, RowsWork w, int S, int chunks,
                                                        double chi0,
                                                        const double* __restrict__ theta,
                                                        double* __restrict__ out,
