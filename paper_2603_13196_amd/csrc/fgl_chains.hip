@@ -38,6 +38,7 @@
 #include "fgl_host.h"
 #include "fgl_philox.h"
 #include "fgl_pow2.h"
+#include "fgl_wave.h"
 
 #include <algorithm>
 #include <cmath>
@@ -186,7 +187,7 @@ __device__ __forceinline__ void new_step(const ChainState& s, int i, Scal& c, in
     }
   }
   nrm = wave_sum(nrm);
-  __builtin_amdgcn_wave_barrier();                      // u written by all lanes
+  wave_sync();                                          // u written by all lanes
   const double inv = 1.0 / sqrt(nrm);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {                         // dir = L u, L lower triangular
@@ -196,7 +197,7 @@ __device__ __forceinline__ void new_step(const ChainState& s, int i, Scal& c, in
     for (int k = 0; k <= j; ++k) acc += s.chol[(size_t)j * P + k] * u[k];
     v.d[q] = acc * inv;
   }
-  __builtin_amdgcn_wave_barrier();                      // u read by all lanes
+  wave_sync();                                          // u read by all lanes
   double r, unused;
   uniform2(s, i, c.ctr + np, r, unused);
   c.ctr += np + 1;
@@ -711,8 +712,7 @@ __global__ __launch_bounds__(kRunMaxThreads) void k_chain_run(ChainState s, DevM
           }
         }
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();              // a group's four lanes are in one wave
+      wave_sync();                                  // a group's four lanes are in one wave
       if (f < F && (id & 3) == 0) {
         // channels in order, time bins in order: one chain of fmas, its
         // residuals read eight ahead
@@ -736,7 +736,7 @@ __global__ __launch_bounds__(kRunMaxThreads) void k_chain_run(ChainState s, DevM
         }
         s_part[f >> 2] = acc;
       }
-      __builtin_amdgcn_wave_barrier();              // s_r is free for the next channels
+      wave_sync();                                  // s_r is free for the next channels
     }
     __syncthreads();
   }

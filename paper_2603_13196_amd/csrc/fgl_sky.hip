@@ -27,6 +27,7 @@
 // (Algs. method1 and method2) is a short sequential computation on the
 // host.
 #include "fgl_host.h"
+#include "fgl_wave.h"
 
 #include <algorithm>
 #include <cmath>
@@ -445,11 +446,14 @@ __global__ __launch_bounds__(256) void k_sky_regions(SkyDev s, const double* __r
       const unsigned long long m = __ballot((j >> k) & 1);
       same &= (j >> k) & 1 ? m : ~m;
     }
-    if (j < 0) continue;
-    const int fill = s_cnt[j], at = fill + __popcll(same & before);
-    order[(size_t)ring * L + at] = c;
-    asort[(size_t)ring * L + at] = omega * s.t_ex[row + c];
-    if ((same & ~before) == (1ull << tid)) s_cnt[j] = at + 1;   // the region's last lane
+    const int at = j < 0 ? 0 : s_cnt[j] + __popcll(same & before);
+    if (j >= 0) {
+      order[(size_t)ring * L + at] = c;
+      asort[(size_t)ring * L + at] = omega * s.t_ex[row + c];
+    }
+    wave_sync();                                    // every lane has its run's fill
+    if (j >= 0 && (same & ~before) == (1ull << tid)) s_cnt[j] = at + 1;   // the region's last lane
+    wave_sync();                                    // and meets the new one
   }
   // the runs' padding: up to the next start, a multiple of four
   for (int j = tid; j < N; j += 64)
