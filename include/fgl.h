@@ -252,7 +252,10 @@ int fgl_get_tile(fgl_model* m, int B, int prec, int* waves, int* chans,
 
 /* Measure the candidate tiles for (model, B, prec) now and keep the
  * fastest for later calls, and in the tuner cache.  Synchronous; uses the
- * device. */
+ * device.  A small batch of a small model (FGL_FORM_THIN; at most 2048 rows,
+ * by a measured rule) runs as one launch, which has no tile: the tile measured
+ * for it is that of its size class's calls that take the three launches (row
+ * preparation, likelihood, finalize). */
 int fgl_tune(fgl_model* m, int B, int prec);
 
 /*
@@ -263,7 +266,8 @@ int fgl_tune(fgl_model* m, int B, int prec);
  * the cached one when it is still a candidate for it, else the default.
  * path: a file of one JSON object per line,
  *   {"arch":"gfx950","kind":0,"N":32,...,"bucket":16384,"waves":8,"fc":8,"occ":3}
- * whose entries are loaded now (a missing file is an empty cache) and which
+ * (with "staged":1 after the bucket where its smallest batches run as one
+ * launch), whose entries are loaded now (a missing file is an empty cache) and which
  * is rewritten after every tuning; NULL stops writing.  The environment
  * variable FGL_TUNE_CACHE names such a file for the process when this is
  * never called.  Tiles never change results.  Returns FGL_OK.

@@ -692,10 +692,11 @@ Tile default_tile(Kind k, const DevModel& d, int B) {
 // ---------------------------------------------------------------------------
 // one call: prep -> main -> finalize on stream s
 
+// staged: the three launches, also where one would do
 int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb, const double* d_theta,
-            int B, double* d_out, hipStream_t s) {
+            int B, double* d_out, hipStream_t s, bool staged) {
   // a small thin batch is one launch: the three below do their part or nothing
-  wb.w.thin_rows = thin_rows_of(k, m->dm, tile, B, d_theta, d_out);
+  wb.w.thin_rows = staged ? 0 : thin_rows_of(k, m->dm, tile, B, d_theta, d_out);
   wb.w.theta = d_theta;
   wb.w.out = d_out;
   const int rc = enqueue_partials(m, k, tile, wb, d_theta, B, s);
@@ -824,12 +825,16 @@ std::atomic<uint64_t> g_tc_gen{1};         // bumped whenever the cache changes
 // The fields that fix a model's candidate tiles and their speeds.
 std::string tc_key(const Model* m, Kind k, int bucket) {
   const DevModel& d = m->dm;
+  // buckets whose smallest batch runs as one launch are marked: entries without the
+  // mark may come from timings of that launch, the same for every tile
+  const int least = bucket > 256 ? bucket / 2 + 1 : 1;
+  const bool mark = thin_rows_of(k, d, default_tile(k, d, least), least) > 0;
   char buf[256];
   std::snprintf(buf, sizeof buf,
                 "\"arch\":\"%s\",\"kind\":%d,\"N\":%d,\"NA\":%d,\"F\":%d,\"T\":%d,"
-                "\"proj\":%d,\"pplain\":%d,\"thin\":%d,\"bucket\":%d",
+                "\"proj\":%d,\"pplain\":%d,\"thin\":%d,\"bucket\":%d%s",
                 m->arch.c_str(), (int)k, d.N, d.NA, d.F, d.T, d.proj, d.pplain,
-                d.thin, bucket);
+                d.thin, bucket, mark ? ",\"staged\":1" : "");
   return buf;
 }
 
@@ -937,7 +942,9 @@ int bucket_of(int B) {
 }
 
 // Time every candidate tile on the rows already staged in wb (device theta)
-// and remember the fastest for this (precision, B bucket).
+// and remember the fastest for this (precision, B bucket).  What is timed are
+// the three launches, which a tile is for: a call that runs as one launch has
+// none, but the bucket's larger batches, shared launches and chain rounds do.
 int tune(Model* m, Kind k, WorkBuf& wb, const double* d_theta, int B,
          double* d_out, hipStream_t s) {
   std::vector<Tile> cand = candidates(k, m->dm);
@@ -961,7 +968,7 @@ int tune(Model* m, Kind k, WorkBuf& wb, const double* d_theta, int B,
       rc = ensure_work(m, wb, B, n_groups(m->dm, t), false);
       if (rc != FGL_OK) break;
       (void)hipEventRecord(e0, s);
-      rc = enqueue(m, k, t, wb, d_theta, B, d_out, s);  // warm-up
+      rc = enqueue(m, k, t, wb, d_theta, B, d_out, s, true);  // warm-up
       (void)hipEventRecord(e1, s);
       if (rc != FGL_OK) break;
       if ((e = hipEventSynchronize(e1)) != hipSuccess) {
@@ -973,7 +980,7 @@ int tune(Model* m, Kind k, WorkBuf& wb, const double* d_theta, int B,
       const int reps = ms > 0.0f ? std::max(5, std::min(40, (int)std::ceil(3.0f / ms))) : 5;
       (void)hipEventRecord(e0, s);
       for (int r = 0; r < reps && rc == FGL_OK; ++r)
-        rc = enqueue(m, k, t, wb, d_theta, B, d_out, s);
+        rc = enqueue(m, k, t, wb, d_theta, B, d_out, s, true);
       (void)hipEventRecord(e1, s);
       if ((e = hipEventSynchronize(e1)) != hipSuccess) {
         rc = hip_err(e, "tuning run");

@@ -115,7 +115,7 @@ Tile default_tile(Kind k, const DevModel& d, int B);
 Tile tile_for(Model* m, Kind k, int B);
 int bucket_of(int B);
 int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb,
-            const double* d_theta, int B, double* d_out, hipStream_t s);
+            const double* d_theta, int B, double* d_out, hipStream_t s, bool staged = false);
 int enqueue_partials(Model* m, Kind k, const Tile& tile, WorkBuf& wb,
                      const double* d_theta, int B, hipStream_t s);
 // The likelihood kernel alone, on rows whose records the caller has already

@@ -292,8 +292,9 @@ __host__ __device__ inline int grad_slots(const DevModel& m) { return 4 + m.N * 
 // Values of one region quad's row of 16-row tiles in the gradient kernel's LDS.
 __host__ __device__ inline int grad_kstride(int tiles) { return tiles * 64 + 4; }
 
-// Rows per workgroup of the one-launch thin kernel for B rows (theta to out), or
-// 0 where the three launches are taken.
+// Rows per workgroup of the one-launch thin kernel for B rows, or 0 where the three
+// launches are taken: by the shapes alone, and for a call from theta to out.
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B);
 int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
                  const double* out);
 size_t thin_rows_lds(const DevModel& m, int rows);

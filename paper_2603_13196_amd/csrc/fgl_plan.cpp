@@ -93,8 +93,7 @@ size_t thin_rows_lds(const DevModel& m, int rows) {
 //   N4 F151 T64 B300 19.4, 25.4     N4 F151 T1 B6000 15.0, 19.0; B16384 23.6, 27.7
 //   N4 F120 T30 B2000 15.4, 16.0    N16 F120 T10 B2000 19.6, 12.7 (c 652, taken)
 //   N10 F151 T1 B6000 18.6, 18.4    N4 F100 T1 B6000 15.4, 14.2 (left out for one line)
-int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
-                 const double* out) {
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B) {
   if (k != kThin || t.group != 4) return 0;
   if ((double)B * m.F * (m.NT * m.T + 12 * m.NT + 2 * m.T) > kThinRowsOps) return 0;
   if (B > kThinRowsMax) return 0;
@@ -102,12 +101,16 @@ int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* 
   const int64_t turns = ((m.F + 3) / 4 * rows + 255) / 256;
   const int64_t c = 12 * m.NT + m.T * (m.NT + 30);
   if ((turns - 1) * c > 450 || c > (rows == 4 ? 1650 : 1000)) return 0;
-  if (thin_rows_lds(m, rows) > 48 * 1024) return 0;
+  return thin_rows_lds(m, rows) > 48 * 1024 ? 0 : rows;
+}
+
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
+                 const double* out) {
   // results over the rows they come from: every row is read before any is written
   // only by the three launches
   const char *t0 = reinterpret_cast<const char*>(theta), *o0 = reinterpret_cast<const char*>(out);
   if (o0 < t0 + (size_t)B * m.P * 8 && t0 < o0 + (size_t)B * 8) return 0;
-  return rows;
+  return thin_rows_of(k, m, t, B);
 }
 
 uint64_t variant_of(Kind k, const DevModel& m, const Tile& t) {
