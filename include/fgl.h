@@ -275,7 +275,8 @@ int fgl_tune(fgl_model* m, int B, int prec);
 int fgl_tune_cache(const char* path);
 
 /* Force the tile for (model, B's size class, prec); FGL_EINVAL unless it is
- * one of the tuner's candidates for this model.  Results are unchanged. */
+ * one of the tuner's candidates for this model.  Results are unchanged.  Calls
+ * of that class run with it, as three launches, until a tuning replaces it. */
 int fgl_set_tile(fgl_model* m, int B, int prec, int waves, int chans,
                  int occupancy);
 

@@ -1433,6 +1433,7 @@ int fgl_set_tile(fgl_model* mh, int B, int prec, int waves, int chans, int occup
     if (t.waves == waves && t.fc == chans && t.occ == occupancy) {
       const uint64_t key = ((uint64_t)k << 32) | (uint32_t)bucket_of(std::max(B, 1));
       m->tiles[key] = t;
+      m->tiles[key].chosen = true;
       return FGL_OK;
     }
   }

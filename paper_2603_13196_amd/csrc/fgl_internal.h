@@ -102,6 +102,7 @@ struct Tile {
   int fc;      // frequency channels staged per workgroup
   int group;   // channels per reduction group
   int occ;     // waves per SIMD the kernel is compiled for (2 or 3)
+  bool chosen = false;   // by fgl_set_tile: the call runs it, not one launch (thin_rows_of)
 };
 
 // Channel chunks of a likelihood launch: `nbig` chunks of `fc` channels,

@@ -93,8 +93,10 @@ size_t thin_rows_lds(const DevModel& m, int rows) {
 //   N4 F151 T64 B300 19.4, 25.4     N4 F151 T1 B6000 15.0, 19.0; B16384 23.6, 27.7
 //   N4 F120 T30 B2000 15.4, 16.0    N16 F120 T10 B2000 19.6, 12.7 (c 652, taken)
 //   N10 F151 T1 B6000 18.6, 18.4    N4 F100 T1 B6000 15.4, 14.2 (left out for one line)
+//
+// A tile that the caller chose has to run: such calls stay with the three launches.
 int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B) {
-  if (k != kThin || t.group != 4) return 0;
+  if (k != kThin || t.group != 4 || t.chosen) return 0;
   if ((double)B * m.F * (m.NT * m.T + 12 * m.NT + 2 * m.T) > kThinRowsOps) return 0;
   if (B > kThinRowsMax) return 0;
   const int rows = B <= 1024 ? 4 : 8;

@@ -3,7 +3,7 @@
 // one-launch kernel of small thin batches.  Test infrastructure only.
 //
 //   1. the one-launch rule on both sides of each of its lines, from device and
-//      host memory, and on results over the rows;
+//      host memory, on results over the rows and after fgl_set_tile;
 //   2. the tuner times its candidates as three launches, where the tuned batch
 //      itself is one launch too, and a tile of the bucket is the one it measured;
 //   3. cache entries of such buckets from timings of the one-launch kernel are
@@ -110,6 +110,20 @@ void rule() {
   }
 }
 
+void chosen_tiles() {
+  fgl_model* m = model(4, 151, 1);
+  CHECK(device_call(m, 1000) == 4, "one launch");
+  for (int waves : {1, 2, 4}) {
+    CHECK(fgl_set_tile(m, 1000, FGL_PREC_MIXED, waves, 4, 2) == FGL_OK, "set_tile");
+    CHECK(device_call(m, 1000) == 0 && g_seen.back().tile.waves == waves, "tile %d does not run", waves);
+    CHECK(host_call(m, 900) == 0, "host call after set_tile");
+    CHECK(device_call(m, 400) == 4, "another size class");
+  }
+  CHECK(fgl_tune(m, 1000, FGL_PREC_MIXED) == FGL_OK, "tune");
+  CHECK(device_call(m, 1000) == 4, "one launch after a tuning");
+  CHECK(fgl_model_destroy(m) == FGL_OK, "destroy");
+}
+
 void tuning(const char* path) {
   std::remove(path);
   CHECK(fgl_tune_cache(path) == FGL_OK, "cache");
@@ -164,6 +178,7 @@ void saved_tiles(const char* path) {
 int main(int argc, char** argv) {
   const std::string path = argc > 1 ? argv[1] : "route_tiles.jsonl";
   rule();
+  chosen_tiles();
   tuning(path.c_str());
   saved_tiles(path.c_str());
   std::printf("checks failed: %ld, stand-in reports: %ld\n", g_fail, stub_errors());
