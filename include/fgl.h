@@ -290,7 +290,9 @@ size_t fgl_model_bytes(const fgl_model* m);
  * on m (n = 1: every call), on the stream that kernel runs on (graph replay
  * is bypassed meanwhile).  The events carry no system-scope fence; each pair
  * still adds a few microseconds to its call, which n > 1 spreads over n
- * calls.  fgl_kernel_timing(m, 0) stops recording; n < 0 is FGL_EINVAL.
+ * calls.  A recorded call takes its row preparation, likelihood and finalize
+ * kernels also where it would run as one launch.
+ * fgl_kernel_timing(m, 0) stops recording; n < 0 is FGL_EINVAL.
  * fgl_kernel_time waits for the recorded kernels and returns their summed
  * duration (ms) and count.
  */

@@ -692,11 +692,19 @@ Tile default_tile(Kind k, const DevModel& d, int B) {
 // ---------------------------------------------------------------------------
 // one call: prep -> main -> finalize on stream s
 
+// Rows per workgroup of the next call as one launch, or 0: a call whose likelihood
+// kernel is timed runs it by itself.
+static int one_launch_rows(const Model* m, Kind k, const Tile& tile, int B, const double* theta,
+                           const double* out) {
+  if (m->timing > 0 && m->timing_n % (uint64_t)m->timing == 0) return 0;
+  return thin_rows_of(k, m->dm, tile, B, theta, out);
+}
+
 // staged: the three launches, also where one would do
 int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb, const double* d_theta,
             int B, double* d_out, hipStream_t s, bool staged) {
   // a small thin batch is one launch: the three below do their part or nothing
-  wb.w.thin_rows = staged ? 0 : thin_rows_of(k, m->dm, tile, B, d_theta, d_out);
+  wb.w.thin_rows = staged ? 0 : one_launch_rows(m, k, tile, B, d_theta, d_out);
   wb.w.theta = d_theta;
   wb.w.out = d_out;
   const int rc = enqueue_partials(m, k, tile, wb, d_theta, B, s);
@@ -1195,7 +1203,7 @@ int fgl_loglike_batch(fgl_model* mh, const double* theta, int B, double* out, in
   }
   // a one-launch call reads its rows from the pinned staging and writes its
   // results there: neither copies nor a graph
-  if (thin_rows_of(k, m->dm, tile, B, wb.h_theta, wb.h_out) > 0) {
+  if (one_launch_rows(m, k, tile, B, wb.h_theta, wb.h_out) > 0) {
     if ((rc = enqueue(m, k, tile, wb, wb.h_theta, B, wb.h_out, s)) != FGL_OK) return rc;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_err(e, "hipStreamSynchronize");
     std::memcpy(out, wb.h_out, (size_t)B * 8);

@@ -6,7 +6,8 @@
 //      host memory, on results over the rows and after fgl_set_tile;
 //   2. the tuner times its candidates as three launches, where the tuned batch
 //      itself is one launch too, and a tile of the bucket is the one it measured;
-//   3. cache entries of such buckets from timings of the one-launch kernel are
+//   3. kernel timing covers the likelihood kernel alone;
+//   4. cache entries of such buckets from timings of the one-launch kernel are
 //      not used, others are.
 // Prints "checks failed: 0" when all hold.
 #define launch_main stand_in_launch_main
@@ -173,6 +174,20 @@ void saved_tiles(const char* path) {
   CHECK(fgl_tune_cache(nullptr) == FGL_OK, "cache");
 }
 
+void timing() {
+  fgl_model* m = model(4, 151, 1);
+  CHECK(device_call(m, 500) == 4, "one launch");
+  CHECK(fgl_kernel_timing(m, 2) == FGL_OK, "timing");
+  for (int c = 0; c < 6; ++c) CHECK(device_call(m, 500) == (c % 2 ? 4 : 0), "timed call %d", c);
+  for (int c = 0; c < 4; ++c) CHECK(host_call(m, 500) == (c % 2 ? 4 : 0), "timed host call %d", c);
+  double ms = 0.0;
+  int64_t n = 0;
+  CHECK(fgl_kernel_time(m, &ms, &n) == FGL_OK && n == 5, "%lld recorded", (long long)n);
+  CHECK(fgl_kernel_timing(m, 0) == FGL_OK, "timing");
+  CHECK(device_call(m, 500) == 4, "one launch");
+  CHECK(fgl_model_destroy(m) == FGL_OK, "destroy");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -181,6 +196,7 @@ int main(int argc, char** argv) {
   chosen_tiles();
   tuning(path.c_str());
   saved_tiles(path.c_str());
+  timing();
   std::printf("checks failed: %ld, stand-in reports: %ld\n", g_fail, stub_errors());
   return g_fail || stub_errors() ? 1 : 0;
 }
