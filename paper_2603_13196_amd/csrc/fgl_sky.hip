@@ -1060,11 +1060,13 @@ int run_lag(Sky* sk, const Lag& p, const int32_t* shifts, int T, double* importa
                      tasks, tstart, W, bper, part);
   hipLaunchKernelGGL(k_sky_reduce, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, part, nch,
                      np, imp);
+  // the map is copied only where every weight is positive: a refused call leaves
+  // the caller's as it was
   int first = none;
   if ((e = hipGetLastError()) == hipSuccess &&
-      (e = hipMemcpyAsync(importance, imp, np * 8, hipMemcpyDeviceToHost, st)) == hipSuccess &&
-      (e = hipMemcpyAsync(&first, bad, 4, hipMemcpyDeviceToHost, st)) == hipSuccess)
-    e = hipStreamSynchronize(st);
+      (e = hipMemcpyAsync(&first, bad, 4, hipMemcpyDeviceToHost, st)) == hipSuccess &&
+      (e = hipStreamSynchronize(st)) == hipSuccess && first == none)
+    e = hipMemcpy(importance, imp, np * 8, hipMemcpyDeviceToHost);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(st);
     return hip_err(e, "importance kernels");

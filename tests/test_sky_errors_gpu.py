@@ -1,0 +1,36 @@
+"""Importance calls that are refused, on rings wide enough for the lag-grid
+kernels and on narrow ones: a weight that integrates to zero at a step names that
+step's channel and leaves the caller's map as it was."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from workload.sky import Sky, make_sky
+from tests.gpu_util import lib, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _importance(fgl, sm, shifts, scheme, out):
+    sh = np.ascontiguousarray(shifts, dtype=np.int32)
+    return fgl._lib.fgl_sky_importance(sm.handle, sh.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), sh.size,
+                                       fgl.WEIGHTS[scheme], out.ctypes.data_as(fgl._dp))
+
+
+@pytest.mark.parametrize("nlon,T", [(400, 12), (60, 12)])
+def test_refused_maps_are_left_alone(nlon, T):
+    fgl = lib()
+    s = make_sky(6, nlon, np.linspace(50.0, 200.0, 7), T, seed=nlon)
+    beam = np.ascontiguousarray(s.beam + 0.01, dtype=np.float32)
+    beam[5] = 0.0                                    # one channel sees nothing
+    hor = np.ones_like(s.horizon)
+    sm = fgl.SkyModel.from_sky(Sky(s.omega, s.t_ex, s.beta, beam, hor, s.freqs, s.shifts))
+    out = np.full((6, nlon), 7.25)
+    rc = _importance(fgl, sm, np.arange(T), "beam", out)
+    say(f"  {nlon} columns: {rc} {fgl.fgl_last_error()}")
+    assert rc == fgl.FGL_EINVAL and "channel 5, step 0 integrates to 0" in fgl.fgl_last_error()
+    assert np.all(out == 7.25)
+    assert _importance(fgl, sm, np.arange(T), "sky", out) == fgl.FGL_OK
+    assert np.all(np.isfinite(out)) and not np.any(out == 7.25)
+    sm.close()
