@@ -30,6 +30,7 @@
 #include "fgl_wave.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -948,7 +949,7 @@ struct Sky {
   SkyDev d{};
   double nu0 = 0.0;
   hipStream_t stream = nullptr;
-  double last_ms = 0.0;            // last k_sky_k duration (chromatic)
+  std::atomic<double> last_ms{0.0};   // last k_sky_k duration (chromatic), read at any time
   // One call at a time works on a sky: calls are synchronous, and they share its
   // stream and these buffers (SkyCall).
   std::mutex mu;
