@@ -175,8 +175,12 @@ using Int = std::integral_constant<int, V>;
 // groups of four regions per chunk (staged operands in LDS; ND matrix digits).
 // JQ: groups of eight rows that are not all padding, for the projected form with
 // one chunk (the other forms find their last tile's at run time: the branch
-// costs them nothing, and compiled apart their loops spilled more).
-template <int KC, bool PROJ, int AM, int NG, int JQ>
+// costs them nothing, and compiled apart their loops spilled more).  WHOLE: the
+// direct form's row tiles in one loop, the last with all its rows: four chunks and
+// more than one tile, whose registers do not hold a second body (128 regions, 33
+// bins 1950 us with the last tile apart, 1241 in the loop; with one tile, 100 regions
+// and 16 bins, 371 and 936).
+template <int KC, bool PROJ, int AM, int NG, int JQ, bool WHOLE>
 __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork& w, int G, int f0,
                                                int fn, int b, const double* s_tab,
                                                const unsigned char* s_kd, const double* s_D) {
@@ -201,6 +205,15 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
   // a full first chunk leaves the second tile one entry in it: region 31 of the
   // tile's first row, done in FP64
   constexpr bool DIAG = SKIP && KC == 2 && NG == 4;
+  // How the compiler meets the products of the direct form: in place, or (LATE) as
+  // functions of their own that it simplifies before it inlines them.  The loops of
+  // several chunks fill the registers, and which way spills less differs by variant;
+  // all of it in place cost up to half the speed (90 regions, 20 bins 428 us against
+  // 205 before the slots were fitted, and 159 now; three 32-region masks 465, 250 and
+  // 251; with two, 149, 134 and 94; 4 x 20 masks, 64 bins 644, 460 and 434; 201
+  // channels, 4096 rows).
+  constexpr bool LATE = !PROJ && ((KC == 2 && AM != 0) || (KC == 3 && (AM != 0 || NG == 4)) ||
+                                  (KC == 4 && (AM == 1 || !WHOLE)));
   double beta[KC][NJ];
   double off[AM == 1 ? KC : 1][NJ];
   double off1[AM == 2 ? KC : 1];
@@ -375,9 +388,52 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
   // groups of eight rows (a later group holds padding only, whose sums and
   // targets are zero).  QN = 0: `jq` groups (direct form: rows past T masked).
   //
-  // MF(acc, q, p): the product of matrix digit q and power digit p
+  // MF(acc, q, p): the product of matrix digit q and power digit p.  The even levels
+  // (0, 2 and 4) depend on no shift; the odd ones (1, 3 and 5) come after the
+  // shift-adds (direct form: with the constant term's digits).  Macros, so that the
+  // two ways of LATE have one text.
 #define MF(acc, q, p) \
   acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[q][kc - K0], C.B[kc][p], acc, 0, 0, 0)
+#define EVEN_LEVELS()                                         \
+  a0 = a1 = a2 = i32x16{};                                    \
+  _Pragma("unroll") for (int kc = K0; kc < KC; ++kc) {        \
+    MF(a0, 0, 0);                                             \
+    MF(a1, 0, 2); MF(a1, 1, 1); MF(a1, 2, 0);                 \
+    MF(a2, 0, 4); MF(a2, 1, 3); MF(a2, 2, 2); MF(a2, 3, 1);   \
+    if constexpr (PROJ) MF(a2, 4, 0);                         \
+  }
+#define ODD_LEVELS()                                                                     \
+  if constexpr (QN == 4 || QN < 0) {                                                     \
+    a0 = (i32x16)(((u32x16)a0 << 8u) + (PROJ ? 0u : (uint32_t)C.c0));                    \
+    a1 = (i32x16)(((u32x16)a1 << 8u) + (PROJ ? 0u : (uint32_t)C.c1));                    \
+    a2 = (i32x16)(((u32x16)a2 << 8u) + (PROJ ? 0u : (uint32_t)C.c2));                    \
+  } else {                                                                               \
+    _Pragma("unroll") for (int q = 0; q < QM; ++q) {                                     \
+      if (QN == 0 && q >= jq) break;                                                     \
+      _Pragma("unroll") for (int j = 4 * q; j < 4 * q + 4; ++j) {                        \
+        a0[j] = (int32_t)(((uint32_t)a0[j] << 8) + (PROJ ? 0u : (uint32_t)C.c0));        \
+        a1[j] = (int32_t)(((uint32_t)a1[j] << 8) + (PROJ ? 0u : (uint32_t)C.c1));        \
+        a2[j] = (int32_t)(((uint32_t)a2[j] << 8) + (PROJ ? 0u : (uint32_t)C.c2));        \
+      }                                                                                  \
+    }                                                                                    \
+  }                                                                                      \
+  _Pragma("unroll") for (int kc = K0; kc < KC; ++kc) {                                   \
+    MF(a0, 0, 1); MF(a0, 1, 0);                                                          \
+    MF(a1, 0, 3); MF(a1, 1, 2); MF(a1, 2, 1); MF(a1, 3, 0);                              \
+    MF(a2, 0, 5); MF(a2, 1, 4); MF(a2, 2, 3); MF(a2, 3, 2);                              \
+    if constexpr (PROJ) {                                                                \
+      MF(a2, 4, 1); MF(a2, 5, 0);                                                        \
+    }                                                                                    \
+  }
+  auto even_late = [&](auto k0, const auto& A, const Chan& C, i32x16& a0, i32x16& a1, i32x16& a2) {
+    constexpr int K0 = decltype(k0)::value;
+    EVEN_LEVELS()
+  };
+  auto odd_late = [&](auto k0, auto qn, int jq, const auto& A, const Chan& C, i32x16& a0, i32x16& a1,
+                      i32x16& a2) {
+    constexpr int K0 = decltype(k0)::value, QN = decltype(qn)::value, QM = QN > 0 ? QN : 4;
+    ODD_LEVELS()
+  };
   auto tile = [&](int f, int tt, const Chan& C, auto k0, auto qn, int jq = 4) {
     constexpr int K0 = decltype(k0)::value, QN = decltype(qn)::value;
     constexpr int QM = QN > 0 ? QN : 4;
@@ -388,72 +444,54 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
 #pragma unroll
       for (int kc = K0; kc < KC; ++kc)
         A[L][kc - K0] = *reinterpret_cast<const i32x4*>(kf + ((L * KC + kc) * TT + tt) * 1024);
-    // levels 0, 2 and 4 (no dependence on a shift)
-    i32x16 a0 = {}, a1 = {}, a2 = {};
-#pragma unroll
-    for (int kc = K0; kc < KC; ++kc) {
-      MF(a0, 0, 0);
-      MF(a1, 0, 2); MF(a1, 1, 1); MF(a1, 2, 0);
-      MF(a2, 0, 4); MF(a2, 1, 3); MF(a2, 2, 2); MF(a2, 3, 1);
-      if constexpr (PROJ) MF(a2, 4, 0);
-    }
-    // shift-adds (direct form: with the constant term's digits), then levels
-    // 1, 3 and 5
-    if constexpr (QN == 4) {
-      a0 = (i32x16)(((u32x16)a0 << 8u) + (PROJ ? 0u : (uint32_t)C.c0));
-      a1 = (i32x16)(((u32x16)a1 << 8u) + (PROJ ? 0u : (uint32_t)C.c1));
-      a2 = (i32x16)(((u32x16)a2 << 8u) + (PROJ ? 0u : (uint32_t)C.c2));
+    i32x16 a0, a1, a2;
+    if constexpr (LATE) {
+      even_late(k0, A, C, a0, a1, a2);
+      odd_late(k0, qn, jq, A, C, a0, a1, a2);
     } else {
+      EVEN_LEVELS()
+      ODD_LEVELS()
+    }
+    // epilogue: residuals and chi-square
+    const double* Dt = s_D + (size_t)f * TT * 32 + g * 4 + tt * 32;
+    const double s0 = C.e.s0, s1 = C.e.s0 * 0x1.0p-16, s2 = C.e.s0 * 0x1.0p-32;
+    auto residuals = [&](auto ragged) {              // ragged: rows past T are left out
 #pragma unroll
       for (int q = 0; q < QM; ++q) {
         if (QN == 0 && q >= jq) break;
 #pragma unroll
         for (int j = 4 * q; j < 4 * q + 4; ++j) {
-          a0[j] = (int32_t)(((uint32_t)a0[j] << 8) + (PROJ ? 0u : (uint32_t)C.c0));
-          a1[j] = (int32_t)(((uint32_t)a1[j] << 8) + (PROJ ? 0u : (uint32_t)C.c1));
-          a2[j] = (int32_t)(((uint32_t)a2[j] << 8) + (PROJ ? 0u : (uint32_t)C.c2));
-        }
-      }
-    }
-#pragma unroll
-    for (int kc = K0; kc < KC; ++kc) {
-      MF(a0, 0, 1); MF(a0, 1, 0);
-      MF(a1, 0, 3); MF(a1, 1, 2); MF(a1, 2, 1); MF(a1, 3, 0);
-      MF(a2, 0, 5); MF(a2, 1, 4); MF(a2, 2, 3); MF(a2, 3, 2);
-      if constexpr (PROJ) {
-        MF(a2, 4, 1); MF(a2, 5, 0);
-      }
-    }
-    // epilogue: residuals and chi-square
-    const double* Dt = s_D + (size_t)f * TT * 32 + g * 4 + tt * 32;
-    const double s0 = C.e.s0, s1 = C.e.s0 * 0x1.0p-16, s2 = C.e.s0 * 0x1.0p-32;
-#pragma unroll
-    for (int q = 0; q < QM; ++q) {
-      if (QN == 0 && q >= jq) break;
-#pragma unroll
-      for (int j = 4 * q; j < 4 * q + 4; ++j) {
-        double d = Dt[(j >> 2) * 8 + (j & 3)];
-        // projected form: row 0 (element 0 of the first tile in lanes 0..31) is
-        // the mean row, whose target depends on the row b; the first rows of
-        // later tiles have a term in FP64
-        if constexpr (PROJ)
-          if (j == 0) {
-            if constexpr (K0 > 0) d = DIAG && g == 0 ? d - C.e.dt : d;
-            else d = tt == 0 && g == 0 ? C.e.t0 : d;
+          double d = Dt[(j >> 2) * 8 + (j & 3)];
+          // projected form: row 0 (element 0 of the first tile in lanes 0..31) is
+          // the mean row, whose target depends on the row b; the first rows of
+          // later tiles have a term in FP64
+          if constexpr (PROJ)
+            if (j == 0) {
+              if constexpr (K0 > 0) d = DIAG && g == 0 ? d - C.e.dt : d;
+              else d = tt == 0 && g == 0 ? C.e.t0 : d;
+            }
+          double r = fma(-s0, (double)a0[j], d);
+          r = fma(-s1, (double)a1[j], r);
+          r = fma(-s2, (double)a2[j], r);
+          if constexpr (decltype(ragged)::value) {
+            const int t = tt * 32 + (j >> 2) * 8 + g * 4 + (j & 3);
+            r = t < m.T ? r : 0.0;
           }
-        double r = fma(-s0, (double)a0[j], d);
-        r = fma(-s1, (double)a1[j], r);
-        r = fma(-s2, (double)a2[j], r);
-        if constexpr (!PROJ && QN == 0) {
-          const int t = tt * 32 + (j >> 2) * 8 + g * 4 + (j & 3);
-          r = t < m.T ? r : 0.0;
+          if (j & 1) acc_b = fma(r, r, acc_b);
+          else acc_a = fma(r, r, acc_a);
         }
-        if (j & 1) acc_b = fma(r, r, acc_b);
-        else acc_a = fma(r, r, acc_a);
       }
+    };
+    if constexpr (QN < 0) {
+      if (tt == TT - 1 && (m.T & 31)) residuals(std::true_type{});   // uniform
+      else residuals(std::false_type{});
+    } else {
+      residuals(std::integral_constant<bool, !PROJ && QN == 0>{});
     }
   };
 #undef MF
+#undef EVEN_LEVELS
+#undef ODD_LEVELS
   // after a channel's last row tile: the peeled row, the partial
   auto tail = [&](int f, const Epi& C) {
     if constexpr (PROJ) {
@@ -496,6 +534,8 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
         if (jq < 4) tile(f, KC - 1, C, Int<KC - 1>{}, Int<0>{}, jq);
         else tile(f, KC - 1, C, Int<KC - 1>{}, Int<4>{});
       }
+    } else if constexpr (WHOLE) {
+      for (int tt = 0; tt < TT; ++tt) tile(f, tt, C, Int<0>{}, Int<-1>{});
     } else {
       for (int tt = 0; tt < TT - 1; ++tt) tile(f, tt, C, Int<0>{}, Int<4>{});
       if (m.T & 31)
@@ -512,7 +552,7 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
 // The body of workgroup `block` of a launch on (m, w); the kernels below
 // call it for one model (k_mixed) or for several that share the compiled
 // variant (k_mixed_multi).
-template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0>
+template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0, bool WHOLE = false>
 __device__ __forceinline__ void mixed_body(const DevModel& m, const RowsWork& w, const Chunks& cp,
                                            int G, int nb, int block) {
   constexpr int ND = PROJ ? kProjDigits : 4;       // digits of the matrix rows
@@ -537,8 +577,8 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const RowsWork& w,
   __syncthreads();
   const int b = bt * (W * 32) + wave * 32 + (lane & 31);
   auto run = [&](auto ng, auto jq) {
-    mixed_channels<KC, PROJ, AM, decltype(ng)::value, decltype(jq)::value>(m, w, G, f0, fn, b,
-                                                                           s_tab, s_kd, s_D);
+    mixed_channels<KC, PROJ, AM, decltype(ng)::value, decltype(jq)::value, WHOLE>(
+        m, w, G, f0, fn, b, s_tab, s_kd, s_D);
   };
   // groups of four regions per lane and chunk and, for one chunk (8 NG + 1 rows
   // at most), of eight rows: each as its own loop, since a choice inside the loop
@@ -562,13 +602,13 @@ __device__ __forceinline__ void mixed_body(const DevModel& m, const RowsWork& w,
 }
 
 // NG: the groups of four regions the model has, where a kernel of its own for
-// them pays (one alpha per region on several chunks: 3 % over two loops in one
-// kernel, which spill more around them); 0: chosen in the kernel.
-template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0>
+// them pays (the direct form and one alpha per region on several chunks: two loops
+// in one kernel spill more around them); 0: chosen in the kernel.
+template <int W, int KC, bool PROJ, int OCC, int AM, int NG = 0, bool WHOLE = false>
 __global__ __launch_bounds__(W * 64)
 __attribute__((amdgpu_waves_per_eu(OCC, OCC))) void k_mixed(DevModel m, RowsWork w, Chunks cp,
                                                     int G, int nb) {
-  mixed_body<W, KC, PROJ, OCC, AM, NG>(m, w, cp, G, nb, blockIdx.x);
+  mixed_body<W, KC, PROJ, OCC, AM, NG, WHOLE>(m, w, cp, G, nb, blockIdx.x);
 }
 
 // The group of workgroup blockIdx.x in launch `which` (0 likelihood, 1 row
@@ -957,7 +997,7 @@ __global__ __launch_bounds__(256) void k_prep_thin64(DevModel m, const double* _
         const float4* kf = reinterpret_cast<const float4*>(m.kthin) + (size_t)f * T * (NT / 4);
         const double* Df = m.D + (size_t)f * m.TT * 32;
         // U bins at a time, so that their loads and chains overlap
-        constexpr int U = NT <= 4 ? 8 : NT <= 8 ? 4 : 2;
+        constexpr int U = thin_rows_bins(NT);
         for (int t0 = 0; t0 < T; t0 += U) {
           float4 k[U][NT / 4];
           double dv[U], ms[U];
@@ -1560,20 +1600,30 @@ hipError_t mixed_wa(const DevModel& m, const Work& w, const Chunks& cp, int G, i
         if constexpr (AM == 1)
           return m.ng == 4 ? go_mixed(k_mixed<W, 2, true, 2, 1, 4>, nb, lds, s, m, w, cp, G, th)
                            : go_mixed(k_mixed<W, 2, true, 2, 1, 3>, nb, lds, s, m, w, cp, G, th);
-        return go_mixed(k_mixed<W, 2, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
+        else
+          return go_mixed(k_mixed<W, 2, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
       case 3:
         if constexpr (AM == 1)
           return m.ng == 4 ? go_mixed(k_mixed<W, 3, true, 2, 1, 4>, nb, lds, s, m, w, cp, G, th)
                            : go_mixed(k_mixed<W, 3, true, 2, 1, 3>, nb, lds, s, m, w, cp, G, th);
-        return go_mixed(k_mixed<W, 3, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
+        else
+          return go_mixed(k_mixed<W, 3, true, 2, AM>, nb, lds, s, m, w, cp, G, th);
       default: return hipErrorInvalidValue;
     }
   }
   switch (m.KC) {
     case 1: return go_mixed(k_mixed<W, 1, false, 2, AM>, nb, lds, s, m, w, cp, G, th);
-    case 2: return go_mixed(k_mixed<W, 2, false, 2, AM>, nb, lds, s, m, w, cp, G, th);
-    case 3: return go_mixed(k_mixed<W, 3, false, 2, AM>, nb, lds, s, m, w, cp, G, th);
-    case 4: return go_mixed(k_mixed<W, 4, false, 2, AM>, nb, lds, s, m, w, cp, G, th);
+    case 2:
+      if constexpr (AM != 2)
+        if (m.ng == 3) return go_mixed(k_mixed<W, 2, false, 2, AM, 3>, nb, lds, s, m, w, cp, G, th);
+      return go_mixed(k_mixed<W, 2, false, 2, AM, 4>, nb, lds, s, m, w, cp, G, th);
+    case 3:
+      if constexpr (AM != 2)
+        if (m.ng == 3) return go_mixed(k_mixed<W, 3, false, 2, AM, 3>, nb, lds, s, m, w, cp, G, th);
+      return go_mixed(k_mixed<W, 3, false, 2, AM, 4>, nb, lds, s, m, w, cp, G, th);
+    case 4:
+      return m.TT > 1 ? go_mixed(k_mixed<W, 4, false, 2, AM, 4, true>, nb, lds, s, m, w, cp, G, th)
+                      : go_mixed(k_mixed<W, 4, false, 2, AM, 4>, nb, lds, s, m, w, cp, G, th);
     default: return hipErrorInvalidValue;
   }
 }
