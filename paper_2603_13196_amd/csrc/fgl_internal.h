@@ -298,6 +298,8 @@ __host__ __device__ inline int grad_kstride(int tiles) { return tiles * 64 + 4; 
 int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B);
 int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
                  const double* out);
+// Time bins that kernel takes at a time.
+__host__ __device__ constexpr int thin_rows_bins(int NT) { return NT <= 4 ? 8 : NT <= 8 ? 4 : 2; }
 size_t thin_rows_lds(const DevModel& m, int rows);
 // Launch shape of the gradient kernel for B rows: 4-wave workgroups of 64
 // rows, `chunks` channel chunks of `per` channels, staged `fs` at a time.

@@ -178,8 +178,8 @@ using Int = std::integral_constant<int, V>;
 // costs them nothing, and compiled apart their loops spilled more).  WHOLE: the
 // direct form's row tiles in one loop, the last with all its rows: four chunks and
 // more than one tile, whose registers do not hold a second body (128 regions, 33
-// bins 1950 us with the last tile apart, 1241 in the loop; with one tile, 100 regions
-// and 16 bins, 371 and 936).
+// bins 1949 us with the last tile apart, 1166 in the loop; with one tile, 100 regions
+// and 16 bins, 376 and 936).
 template <int KC, bool PROJ, int AM, int NG, int JQ, bool WHOLE>
 __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork& w, int G, int f0,
                                                int fn, int b, const double* s_tab,
@@ -207,11 +207,12 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
   constexpr bool DIAG = SKIP && KC == 2 && NG == 4;
   // How the compiler meets the products of the direct form: in place, or (LATE) as
   // functions of their own that it simplifies before it inlines them.  The loops of
-  // several chunks fill the registers, and which way spills less differs by variant;
-  // all of it in place cost up to half the speed (90 regions, 20 bins 428 us against
-  // 205 before the slots were fitted, and 159 now; three 32-region masks 465, 250 and
-  // 251; with two, 149, 134 and 94; 4 x 20 masks, 64 bins 644, 460 and 434; 201
-  // channels, 4096 rows).
+  // several chunks fill the registers, and which way spills less differs by variant.
+  // Whole calls at 201 channels and 4096 rows (us): every loop in place and two slot
+  // counts in a kernel, all slots computed, now:
+  //   90 regions, 20 bins 426, 205, 157      6 x 16 masks, 20 bins 466, 250, 251
+  //   3 x 16 masks, 20 bins 149, 134, 93     5 x 12 masks, 50 bins 283, 262, 224
+  //   4 x 20 masks, 64 bins 664, 458, 432    100 regions, 64 bins 2472, 1534, 1176
   constexpr bool LATE = !PROJ && ((KC == 2 && AM != 0) || (KC == 3 && (AM != 0 || NG == 4)) ||
                                   (KC == 4 && (AM == 1 || !WHOLE)));
   double beta[KC][NJ];
