@@ -56,6 +56,8 @@ struct SkyDev {
   const float4* beam4;   // [ceil(F / 4)][nlat][nlon]: channels 4 b .. 4 b + 3 of a
                          // pixel side by side (zero past the last channel)
   const uint8_t* seen;   // [nlat][nlon] some channel's beam is non-zero, antenna frame
+  int finite;            // every weight omega T_sky and omega t_ex is: only then is its
+                         // product with a zero zero, and may be left out
 };
 
 int pad_to(int n, int m) { return (n + m - 1) / m * m; }
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(256) void k_sky_regions(SkyDev s, const double* __r
     int j = lo - 1;
     if (b == edges[N]) j = N - 1;
     if (b < edges[0] || b > edges[N]) j = -1;
-    bool up = false;
+    bool up = !s.finite;
     for (int t = 0; t < T && !up; ++t) {
       const int h = c - shifts[t];
       up = s_seen[h < 0 ? h + nlon : h];
@@ -1325,16 +1327,23 @@ int fgl_sky_create(int nlat, int nlon, int F, const double* omega, const double*
   const size_t np = (size_t)nlat * nlon;
   for (int r = 0; r < nlat; ++r)
     if (!(omega[r] > 0.0) || !std::isfinite(omega[r])) return set_err(FGL_EINVAL, "omega[%d] must be finite and > 0", r);
-  for (size_t k = 0; k < np; ++k)
+  double most_t = 0.0, most_b = 0.0, most_lr = 0.0;
+  for (size_t k = 0; k < np; ++k) {
     if (!std::isfinite(t_ex[k]) || !std::isfinite(beta[k]) || std::fabs(beta[k]) > 64.0)
       return set_err(FGL_EINVAL, "t_ex/beta[%zu] must be finite with |beta| <= 64", k);
+    most_t = std::max(most_t, std::fabs(t_ex[k]));
+    most_b = std::max(most_b, std::fabs(beta[k]));
+  }
   for (size_t k = 0; k < np * F; ++k)
     if (!std::isfinite(beam[k])) return set_err(FGL_EINVAL, "beam[%zu] is not finite", k);
   std::vector<double> lr(F);
   for (int f = 0; f < F; ++f) {
     if (!(freqs[f] > 0.0) || !std::isfinite(freqs[f])) return set_err(FGL_EINVAL, "freqs[%d] must be finite and > 0", f);
     lr[f] = std::log2(freqs[f] / nu0);
+    most_lr = std::max(most_lr, std::fabs(lr[f]));
   }
+  const double most_a = most_t * std::exp2(most_b * most_lr) + std::fabs(t_cmb);
+  const double most_omega = *std::max_element(omega, omega + nlat);
   int dev = 0;
   int rc = check_device(&dev);
   if (rc != FGL_OK) return rc;
@@ -1346,6 +1355,7 @@ int fgl_sky_create(int nlat, int nlon, int F, const double* omega, const double*
   sk->d.nlon = nlon;
   sk->d.F = F;
   sk->d.t_cmb = t_cmb;
+  sk->d.finite = std::isfinite(2.0 * most_a) && std::isfinite(2.0 * most_a * most_omega) ? 1 : 0;
   double *om = nullptr, *tx = nullptr, *bt = nullptr, *l2 = nullptr;
   float* bm = nullptr;
   uint8_t* hz = nullptr;
@@ -1410,7 +1420,9 @@ int fgl_sky_importance(fgl_sky* sh, const int32_t* shifts, int T, int scheme, do
     return set_err(FGL_EINVAL, "nlon=%d does not fit one workgroup's LDS", sk->d.nlon);
   const size_t imp_lds = (size_t)T * 36 + (size_t)sk->d.nlon * 32;
   Lag lag;
-  const bool on_grid = imp_lds <= 160 * 1024 && lag_plan(shifts, T, sk->d.nlon, &lag);
+  // (skies with weights past the type's range stay with the kernels that form every
+  // product, and so refuse them)
+  const bool on_grid = sk->d.finite && imp_lds <= 160 * 1024 && lag_plan(shifts, T, sk->d.nlon, &lag);
   hipError_t e = hipSetDevice(sk->dev);
   if (e != hipSuccess) return hip_err(e, "hipSetDevice");
   SkyCall call(sk);
