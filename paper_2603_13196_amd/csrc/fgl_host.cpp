@@ -694,17 +694,17 @@ Tile default_tile(Kind k, const DevModel& d, int B) {
 
 // Rows per workgroup of the next call as one launch, or 0: a call whose likelihood
 // kernel is timed runs it by itself.
-static int one_launch_rows(const Model* m, Kind k, const Tile& tile, int B, const double* theta,
-                           const double* out) {
+static int one_launch_rows(const Model* m, Kind k, const Tile& tile, int B, bool host,
+                           const double* theta, const double* out) {
   if (m->timing > 0 && m->timing_n % (uint64_t)m->timing == 0) return 0;
-  return thin_rows_of(k, m->dm, tile, B, theta, out);
+  return thin_rows_of(k, m->dm, tile, B, host, theta, out);
 }
 
-// staged: the three launches, also where one would do
 int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb, const double* d_theta,
-            int B, double* d_out, hipStream_t s, bool staged) {
+            int B, double* d_out, hipStream_t s, Route route) {
   // a small thin batch is one launch: the three below do their part or nothing
-  wb.w.thin_rows = staged ? 0 : one_launch_rows(m, k, tile, B, d_theta, d_out);
+  wb.w.thin_rows = route == Route::kStaged ? 0
+                   : one_launch_rows(m, k, tile, B, route == Route::kHost, d_theta, d_out);
   wb.w.theta = d_theta;
   wb.w.out = d_out;
   const int rc = enqueue_partials(m, k, tile, wb, d_theta, B, s);
@@ -836,7 +836,7 @@ std::string tc_key(const Model* m, Kind k, int bucket) {
   // buckets whose smallest batch runs as one launch are marked: entries without the
   // mark may come from timings of that launch, the same for every tile
   const int least = bucket > 256 ? bucket / 2 + 1 : 1;
-  const bool mark = thin_rows_of(k, d, default_tile(k, d, least), least) > 0;
+  const bool mark = thin_rows_of(k, d, default_tile(k, d, least), least, true) > 0;
   char buf[256];
   std::snprintf(buf, sizeof buf,
                 "\"arch\":\"%s\",\"kind\":%d,\"N\":%d,\"NA\":%d,\"F\":%d,\"T\":%d,"
@@ -976,7 +976,7 @@ int tune(Model* m, Kind k, WorkBuf& wb, const double* d_theta, int B,
       rc = ensure_work(m, wb, B, n_groups(m->dm, t), false);
       if (rc != FGL_OK) break;
       (void)hipEventRecord(e0, s);
-      rc = enqueue(m, k, t, wb, d_theta, B, d_out, s, true);  // warm-up
+      rc = enqueue(m, k, t, wb, d_theta, B, d_out, s, Route::kStaged);  // warm-up
       (void)hipEventRecord(e1, s);
       if (rc != FGL_OK) break;
       if ((e = hipEventSynchronize(e1)) != hipSuccess) {
@@ -988,7 +988,7 @@ int tune(Model* m, Kind k, WorkBuf& wb, const double* d_theta, int B,
       const int reps = ms > 0.0f ? std::max(5, std::min(40, (int)std::ceil(3.0f / ms))) : 5;
       (void)hipEventRecord(e0, s);
       for (int r = 0; r < reps && rc == FGL_OK; ++r)
-        rc = enqueue(m, k, t, wb, d_theta, B, d_out, s, true);
+        rc = enqueue(m, k, t, wb, d_theta, B, d_out, s, Route::kStaged);
       (void)hipEventRecord(e1, s);
       if ((e = hipEventSynchronize(e1)) != hipSuccess) {
         rc = hip_err(e, "tuning run");
@@ -1203,8 +1203,8 @@ int fgl_loglike_batch(fgl_model* mh, const double* theta, int B, double* out, in
   }
   // a one-launch call reads its rows from the pinned staging and writes its
   // results there: neither copies nor a graph
-  if (one_launch_rows(m, k, tile, B, wb.h_theta, wb.h_out) > 0) {
-    if ((rc = enqueue(m, k, tile, wb, wb.h_theta, B, wb.h_out, s)) != FGL_OK) return rc;
+  if (one_launch_rows(m, k, tile, B, true, wb.h_theta, wb.h_out) > 0) {
+    if ((rc = enqueue(m, k, tile, wb, wb.h_theta, B, wb.h_out, s, Route::kHost)) != FGL_OK) return rc;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_err(e, "hipStreamSynchronize");
     std::memcpy(out, wb.h_out, (size_t)B * 8);
     return FGL_OK;

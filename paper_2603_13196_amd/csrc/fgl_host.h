@@ -114,8 +114,11 @@ std::vector<Tile> candidates(Kind k, const DevModel& d);
 Tile default_tile(Kind k, const DevModel& d, int B);
 Tile tile_for(Model* m, Kind k, int B);
 int bucket_of(int B);
-int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb,
-            const double* d_theta, int B, double* d_out, hipStream_t s, bool staged = false);
+// What enqueue may run as one launch: rows on the device, rows in the call's pinned
+// staging, or nothing (the tuner's calls).
+enum class Route { kDevice, kHost, kStaged };
+int enqueue(Model* m, Kind k, const Tile& tile, WorkBuf& wb, const double* d_theta, int B,
+            double* d_out, hipStream_t s, Route route = Route::kDevice);
 int enqueue_partials(Model* m, Kind k, const Tile& tile, WorkBuf& wb,
                      const double* d_theta, int B, hipStream_t s);
 // The likelihood kernel alone, on rows whose records the caller has already

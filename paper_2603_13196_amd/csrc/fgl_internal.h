@@ -294,9 +294,10 @@ __host__ __device__ inline int grad_slots(const DevModel& m) { return 4 + m.N * 
 __host__ __device__ inline int grad_kstride(int tiles) { return tiles * 64 + 4; }
 
 // Rows per workgroup of the one-launch thin kernel for B rows, or 0 where the three
-// launches are taken: by the shapes alone, and for a call from theta to out.
-int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B);
-int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
+// launches are taken: by the shapes alone, and for a call from theta to out.  host:
+// the rows come from host memory.
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, bool host);
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, bool host, const double* theta,
                  const double* out);
 // Time bins that kernel takes at a time.
 __host__ __device__ constexpr int thin_rows_bins(int NT) { return NT <= 4 ? 8 : NT <= 8 ? 4 : 2; }

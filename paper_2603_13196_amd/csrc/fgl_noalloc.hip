@@ -106,7 +106,7 @@ extern "C" int fgl_loglike_batch_device_noalloc(fgl_model* mh, const double* d_t
   w.partial = reinterpret_cast<double*>(base + b_beta + b_off + b_rows);
   w.ngroup_cap = ngroups;
   w.gpart = nullptr;
-  w.thin_rows = thin_rows_of(k, m->dm, tile, B, d_theta, d_out);
+  w.thin_rows = thin_rows_of(k, m->dm, tile, B, false, d_theta, d_out);
   w.theta = d_theta;
   w.out = d_out;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);

@@ -75,16 +75,40 @@ size_t thin_rows_lds(const DevModel& m, int rows) {
   return ((size_t)rows * (m.P + m.NT * (m.NA > 0 ? 2 : 1) + groups + 16) + 64) * 8 + rows * 4;
 }
 
+// Times (us) of a call from device memory by the slots its regions take: a turn of
+// the one-launch kernel without its bins and with each step of thin_rows_bins, and
+// the three launches without their bins and with each.
+struct ThinCost {
+  double turn, step, launches, bin;
+};
+static ThinCost thin_cost(int NT) {
+  switch (NT) {
+    case 4: return {1.25, 2.6, 10.3, 0.114};
+    case 8: return {1.9, 1.3, 10.3, 0.30};
+    case 12: return {2.3, 1.0, 10.5, 0.39};
+    case 16: return {2.9, 1.2, 12.2, 0.55};
+    case 24: return {4.1, 1.55, 13.3, 0.85};
+    default: return {5.7, 1.9, 13.2, 0.70};
+  }
+}
+
 // A small batch of a thin model is bound by its three launches, about 12 us and
 // the latency of the four channels that a thread takes in turn.  One kernel can do
 // the whole of it in about 5 us and that latency for each turn its 256 / rows
 // threads per row need to cover the channel groups; it reads K per lane from the
 // caches instead of staging it for 256 rows, so large batches stay with the staged
-// kernel.  A channel's latency goes as c = 12 NT + T (NT + 30), 3.5 ns a unit and
-// four channels a turn, so the extra turns must cost less than 7 us:
-// (turns - 1) c <= 450.  Whole calls, three launches and one (us):
+// kernel.  A channel's latency goes as c = 12 NT + T (NT + 30), about 3.5 ns a unit
+// and four channels a turn: (turns - 1) c <= 450 is the widest range.  Whole calls,
+// three launches and one (us):
 //   N4 F151 T1 B1000 14.9, 7.8; B2000 15.4, 10.7     N32 F301 T1 B1000 20.0, 18.2
 //   N24 F200 T6 B300 21.0, 12.8     N16 F151 T20 B900 26.1, 18.5
+// From host memory the three launches come with two copies, 15-20 us more, and one
+// launch is 1.1 to 1.6 times as fast over all of that range.  From device memory it
+// has to be faster by ThinCost, fitted to timed calls on a grid of shapes (standard
+// deviations of 0.4 to 1.0 us for one launch and 0.2 to 1.6 for three).  Of 3236
+// calls of random shapes that it takes, 24 are slower by more than 2 %, 10 % at worst.
+//   left out: N3 F395 T2 B1292 15.3, 18.9     N2 F200 T45 B200 17.1, 22.1
+//   N4 F301 T9 B200 12.8, 15.9     N30 F301 T1 B1 15.2, 17.9
 // A channel of more than c = 1650 (many bins), or 1000 with eight rows, is slower
 // from the caches even in one turn, and past eight rows for each of the 256 CUs the staged kernel's rows
 // fill the chip too.
@@ -95,7 +119,7 @@ size_t thin_rows_lds(const DevModel& m, int rows) {
 //   N10 F151 T1 B6000 18.6, 18.4    N4 F100 T1 B6000 15.4, 14.2 (left out for one line)
 //
 // A tile that the caller chose has to run: such calls stay with the three launches.
-int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B) {
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, bool host) {
   if (k != kThin || t.group != 4 || t.chosen) return 0;
   if ((double)B * m.F * (m.NT * m.T + 12 * m.NT + 2 * m.T) > kThinRowsOps) return 0;
   if (B > kThinRowsMax) return 0;
@@ -103,16 +127,25 @@ int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B) {
   const int64_t turns = ((m.F + 3) / 4 * rows + 255) / 256;
   const int64_t c = 12 * m.NT + m.T * (m.NT + 30);
   if ((turns - 1) * c > 450 || c > (rows == 4 ? 1650 : 1000)) return 0;
+  if (!host) {
+    const ThinCost w = thin_cost(m.NT);
+    const double bins = (m.T + thin_rows_bins(m.NT) - 1) / thin_rows_bins(m.NT);
+    const double ops = (double)B * m.F * (m.NT * m.T + 12 * m.NT + 2 * m.T);
+    const double one = 3.9 + turns * (w.turn + w.step * bins);
+    const double three = std::max(12.4, w.launches + w.bin * m.T + 3e-5 * m.F * std::min(B, 200) +
+                                            2.8e-8 * ops);
+    if (one > three) return 0;
+  }
   return thin_rows_lds(m, rows) > 48 * 1024 ? 0 : rows;
 }
 
-int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, const double* theta,
+int thin_rows_of(Kind k, const DevModel& m, const Tile& t, int B, bool host, const double* theta,
                  const double* out) {
   // results over the rows they come from: every row is read before any is written
   // only by the three launches
   const char *t0 = reinterpret_cast<const char*>(theta), *o0 = reinterpret_cast<const char*>(out);
   if (o0 < t0 + (size_t)B * m.P * 8 && t0 < o0 + (size_t)B * 8) return 0;
-  return thin_rows_of(k, m, t, B);
+  return thin_rows_of(k, m, t, B, host);
 }
 
 uint64_t variant_of(Kind k, const DevModel& m, const Tile& t) {

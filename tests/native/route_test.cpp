@@ -93,19 +93,23 @@ int device_call(fgl_model* m, int B, bool over = false) {
 }
 
 void rule() {
-  struct Line { int N, F, T, B, rows; };
+  struct Line { int N, F, T, B, device, host; };
   const Line lines[] = {
-      {4, 151, 1, 1, 4},     {4, 151, 1, 1024, 4},  {4, 151, 1, 1025, 8}, {4, 151, 1, 2048, 8},
-      {4, 151, 1, 2049, 0},                                    // rows
-      {16, 120, 10, 2000, 8}, {4, 120, 30, 2000, 0},           // a channel's cost, eight rows
-      {16, 120, 20, 900, 4}, {16, 151, 20, 900, 4}, {8, 120, 40, 900, 4}, {8, 120, 45, 900, 0},   // and four
-      {32, 301, 1, 1000, 4}, {8, 301, 20, 500, 0},             // turns
+      {4, 151, 1, 1, 4, 4},     {4, 151, 1, 1024, 4, 4}, {4, 151, 1, 1025, 8, 8},
+      {4, 151, 1, 2048, 8, 8},  {4, 151, 1, 2049, 0, 0},             // rows
+      {16, 120, 10, 2000, 8, 8}, {4, 120, 30, 2000, 0, 0},           // a channel's cost, eight rows
+      {16, 120, 20, 900, 4, 4}, {16, 151, 20, 900, 4, 4},            // and four
+      {8, 120, 40, 900, 4, 4},  {8, 120, 45, 900, 0, 0},
+      {32, 301, 1, 1000, 4, 4}, {8, 301, 20, 500, 0, 0},             // turns
+      // faster in one launch only where the rows are copied otherwise
+      {3, 395, 2, 1292, 0, 8},  {4, 301, 9, 300, 0, 4}, {4, 301, 8, 300, 4, 4}, {2, 200, 45, 1, 0, 4},
+      {30, 301, 1, 1, 0, 4},    {12, 301, 7, 300, 0, 4}, {12, 301, 4, 300, 4, 4},
   };
   for (const Line& l : lines) {
     fgl_model* m = model(l.N, l.F, l.T);
-    CHECK(device_call(m, l.B) == l.rows, "N%d F%d T%d B%d: rows %d, not %d", l.N, l.F, l.T, l.B,
-          g_seen.back().rows, l.rows);
-    CHECK(host_call(m, l.B) == l.rows, "host N%d F%d T%d B%d", l.N, l.F, l.T, l.B);
+    CHECK(device_call(m, l.B) == l.device, "N%d F%d T%d B%d: rows %d, not %d", l.N, l.F, l.T, l.B,
+          g_seen.back().rows, l.device);
+    CHECK(host_call(m, l.B) == l.host, "host N%d F%d T%d B%d", l.N, l.F, l.T, l.B);
     CHECK(device_call(m, l.B, true) == 0, "over the rows: N%d F%d T%d B%d", l.N, l.F, l.T, l.B);
     CHECK(fgl_model_destroy(m) == FGL_OK, "destroy");
   }
