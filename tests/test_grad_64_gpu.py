@@ -34,10 +34,11 @@ def rounding(w, theta):
     return out
 
 
+@pytest.mark.parametrize("more", [1, 33])
 @pytest.mark.parametrize("N,F,B", [(64, 3, 8), (64, 5, 17), (64, 18, 33), (32, 3, 8), (32, 17, 70)])
-def test_last_row_beside_the_tiles(N, F, B):
+def test_last_row_beside_the_tiles(N, F, B, more):
     fgl, orc = lib(), oracle.load()
-    w = workload.make(N, np.linspace(50.0, 200.0, F), N + 33, B, 600 + N, batch="mixed", rich=True)
+    w = workload.make(N, np.linspace(50.0, 200.0, F), N + more, B, 600 + N, batch="mixed", rich=True)
     rl, rg = orc.grad_w(w)
     m = fgl.Model.from_workload(w)
     assert m.form == "projected"
@@ -48,7 +49,7 @@ def test_last_row_beside_the_tiles(N, F, B):
     bar = 1e-9 * (np.abs(rg) + term_scale(orc, w, w.theta))[ok]
     own = rounding(w, w.theta)[ok]
     d = np.abs(g - rg)[ok]
-    say(f"  N{N} F{F}: max|d|/bar={np.max(d / bar):.3f}, rounding up to {np.max(own / bar):.3f} of the bar, "
+    say(f"  N{N} F{F} T{N + more}: max|d|/bar={np.max(d / bar):.3f}, rounding up to {np.max(own / bar):.3f} of the bar, "
         f"max|d|/both={np.max(d / (bar + own)):.3f}")
     assert np.all(d <= bar + own)
     m.close()

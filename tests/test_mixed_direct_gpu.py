@@ -28,7 +28,7 @@ def test_direct_form(na, nb):
         check(got, ref, "mixed", f"a{na} N{N} T{T}")
         n = 0
         for waves in (4, 8):
-            for chans in (4, 8):
+            for chans in range(1, 9):
                 try:
                     m.set_tile(w.B, "mixed", waves, chans, 2)
                 except fgl.FGLError:
