@@ -1289,6 +1289,7 @@ int fgl_loglike_batch_device(fgl_model* mh, const double* d_theta, int B,
   gk.theta = d_theta;
   gk.out = d_out;
   gk.stream = s;
+  gk.chosen = tile.chosen;
   auto it = m->graphs.find(gk);
   if (it != m->graphs.end() && it->second.exec) {
     if (m->timing > 0) ++m->timing_n;

@@ -36,6 +36,7 @@ struct GraphKey {
   const void* theta = nullptr;
   const void* out = nullptr;
   const void* stream = nullptr;
+  bool chosen = false;         // a forced tile's call is never the one-launch kernel
   bool operator<(const GraphKey& o) const {
     if (kind != o.kind) return kind < o.kind;
     if (B != o.B) return B < o.B;
@@ -44,6 +45,7 @@ struct GraphKey {
     if (occ != o.occ) return occ < o.occ;
     if (theta != o.theta) return theta < o.theta;
     if (out != o.out) return out < o.out;
+    if (chosen != o.chosen) return chosen < o.chosen;
     return stream < o.stream;
   }
 };

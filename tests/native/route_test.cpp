@@ -127,6 +127,32 @@ void chosen_tiles() {
   CHECK(fgl_tune(m, 1000, FGL_PREC_MIXED) == FGL_OK, "tune");
   CHECK(device_call(m, 1000) == 4, "one launch after a tuning");
   CHECK(fgl_model_destroy(m) == FGL_OK, "destroy");
+  // the same where calls are replayed: a call captured as one launch, then the
+  // default tile forced
+  setenv("FGL_DEVICE_GRAPHS", "1", 1);
+  m = model(4, 151, 1);
+  unsetenv("FGL_DEVICE_GRAPHS");
+  const int B = 1000, P = fgl_model_nparams(m);
+  double *th = nullptr, *out = nullptr;
+  CHECK(hipMalloc(reinterpret_cast<void**>(&th), (size_t)B * P * 8) == hipSuccess, "alloc");
+  CHECK(hipMalloc(reinterpret_cast<void**>(&out), (size_t)B * 8) == hipSuccess, "alloc");
+  for (int k = 0; k < B * P; ++k) th[k] = 0.5;
+  auto calls = [&](int rows) {
+    for (int c = 0; c < 4; ++c) {                     // eager, captured, replayed
+      g_seen.clear();
+      CHECK(fgl_loglike_batch_device(m, th, B, out, FGL_PREC_MIXED, nullptr) == FGL_OK, "replayed call");
+      (void)hipDeviceSynchronize();
+      CHECK(g_seen.size() == (c < 2 ? 1u : 0u) && (c > 1 || g_seen[0].rows == rows), "replayed call %d", c);
+    }
+  };
+  calls(4);
+  int waves = 0, chans = 0, occ = 0;
+  CHECK(fgl_get_tile(m, B, FGL_PREC_MIXED, &waves, &chans, &occ) == FGL_OK, "get_tile");
+  CHECK(fgl_set_tile(m, B, FGL_PREC_MIXED, waves, chans, occ) == FGL_OK, "set_tile");
+  calls(0);
+  CHECK(fgl_model_destroy(m) == FGL_OK, "destroy");
+  (void)hipFree(th);
+  (void)hipFree(out);
 }
 
 void tuning(const char* path) {
