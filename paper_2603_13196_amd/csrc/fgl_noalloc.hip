@@ -4,8 +4,9 @@
 // fgl_loglike_batch_device keeps a workspace per (model, stream) and grows
 // it with hipMalloc.  Callers that cannot allocate (code under stream
 // capture, tight serving loops, harnesses that forbid it) call this variant
-// instead: the same row preparation, likelihood kernel and finalize, with the
-// workspace carved out of one file-scope device array per GPU.
+// instead: the same kernels (row preparation, likelihood and finalize, or the one
+// launch of a small thin batch, which needs no workspace), with the workspace carved
+// out of one file-scope device array per GPU.
 //
 // The workspace holds, for B rows padded to Bpad: the transposed spectral
 // indices (and log2 amplitude scales), one row record per row and one
