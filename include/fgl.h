@@ -481,7 +481,7 @@ enum { FGL_PARTITION_HIERARCHICAL = 0, FGL_PARTITION_RECURSIVE = 1 };
  *   t_cmb    CMB temperature (K).
  * All inputs are copied; returns FGL_OK, FGL_EINVAL, FGL_ENOMEM, FGL_EDEVICE.
  * Calls on one sky from several threads run one after another.  A sky keeps
- * work buffers of its calls for the next ones, up to 512 MiB of device memory,
+ * work buffers of its calls for the next ones, up to 1 GiB of device memory,
  * until it is destroyed (a model's HBM budget does not count them).
  */
 int fgl_sky_create(int nlat, int nlon, int F, const double* omega,

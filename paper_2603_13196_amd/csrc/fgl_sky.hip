@@ -970,9 +970,9 @@ void free_buf(Sky::Buf& b) {
 
 // A call at work on a sky.  Its buffers stay for the next call up to
 // kSkyKeepBytes, the largest going first beyond that: allocating and freeing them
-// costs a call 0.2-0.7 ms, and a chromatic call on a 256 x 512 sky of 301 channels
-// and 96 steps has 245 MB.
-constexpr size_t kSkyKeepBytes = size_t(512) << 20;
+// costs a call 0.2-0.7 ms, and a chromatic call on a 256 x 512 sky has 245 MB with
+// 301 channels and 96 steps, 820 MB with 401 and 240.
+constexpr size_t kSkyKeepBytes = size_t(1) << 30;
 struct SkyCall {
   Sky* sk;
   std::lock_guard<std::mutex> lk;
