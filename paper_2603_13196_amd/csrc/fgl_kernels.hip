@@ -426,6 +426,30 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
       MF(a2, 4, 1); MF(a2, 5, 0);                                                        \
     }                                                                                    \
   }
+  // Residuals and chi-square.  RAGGED: rows past T are left out.  Projected form: row
+  // 0 (element 0 of the first tile in lanes 0..31) is the mean row, whose target
+  // depends on the row b; the first rows of later tiles have a term in FP64.
+#define RESIDUALS(RAGGED)                                                     \
+  _Pragma("unroll") for (int q = 0; q < QM; ++q) {                            \
+    if (QN == 0 && q >= jq) break;                                            \
+    _Pragma("unroll") for (int j = 4 * q; j < 4 * q + 4; ++j) {               \
+      double d = Dt[(j >> 2) * 8 + (j & 3)];                                  \
+      if constexpr (PROJ)                                                     \
+        if (j == 0) {                                                         \
+          if constexpr (K0 > 0) d = DIAG && g == 0 ? d - C.e.dt : d;          \
+          else d = tt == 0 && g == 0 ? C.e.t0 : d;                            \
+        }                                                                     \
+      double r = fma(-s0, (double)a0[j], d);                                  \
+      r = fma(-s1, (double)a1[j], r);                                         \
+      r = fma(-s2, (double)a2[j], r);                                         \
+      if constexpr (RAGGED) {                                                 \
+        const int t = tt * 32 + (j >> 2) * 8 + g * 4 + (j & 3);               \
+        r = t < m.T ? r : 0.0;                                                \
+      }                                                                       \
+      if (j & 1) acc_b = fma(r, r, acc_b);                                    \
+      else acc_a = fma(r, r, acc_a);                                          \
+    }                                                                         \
+  }
   auto even_late = [&](auto k0, const auto& A, const Chan& C, i32x16& a0, i32x16& a1, i32x16& a2) {
     constexpr int K0 = decltype(k0)::value;
     EVEN_LEVELS()
@@ -456,43 +480,20 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
     // epilogue: residuals and chi-square
     const double* Dt = s_D + (size_t)f * TT * 32 + g * 4 + tt * 32;
     const double s0 = C.e.s0, s1 = C.e.s0 * 0x1.0p-16, s2 = C.e.s0 * 0x1.0p-32;
-    auto residuals = [&](auto ragged) {              // ragged: rows past T are left out
-#pragma unroll
-      for (int q = 0; q < QM; ++q) {
-        if (QN == 0 && q >= jq) break;
-#pragma unroll
-        for (int j = 4 * q; j < 4 * q + 4; ++j) {
-          double d = Dt[(j >> 2) * 8 + (j & 3)];
-          // projected form: row 0 (element 0 of the first tile in lanes 0..31) is
-          // the mean row, whose target depends on the row b; the first rows of
-          // later tiles have a term in FP64
-          if constexpr (PROJ)
-            if (j == 0) {
-              if constexpr (K0 > 0) d = DIAG && g == 0 ? d - C.e.dt : d;
-              else d = tt == 0 && g == 0 ? C.e.t0 : d;
-            }
-          double r = fma(-s0, (double)a0[j], d);
-          r = fma(-s1, (double)a1[j], r);
-          r = fma(-s2, (double)a2[j], r);
-          if constexpr (decltype(ragged)::value) {
-            const int t = tt * 32 + (j >> 2) * 8 + g * 4 + (j & 3);
-            r = t < m.T ? r : 0.0;
-          }
-          if (j & 1) acc_b = fma(r, r, acc_b);
-          else acc_a = fma(r, r, acc_a);
-        }
-      }
-    };
     if constexpr (QN < 0) {
-      if (tt == TT - 1 && (m.T & 31)) residuals(std::true_type{});   // uniform
-      else residuals(std::false_type{});
+      if (tt == TT - 1 && (m.T & 31)) {              // uniform
+        RESIDUALS(true)
+      } else {
+        RESIDUALS(false)
+      }
     } else {
-      residuals(std::integral_constant<bool, !PROJ && QN == 0>{});
+      RESIDUALS((!PROJ && QN == 0))
     }
   };
 #undef MF
 #undef EVEN_LEVELS
 #undef ODD_LEVELS
+#undef RESIDUALS
   // after a channel's last row tile: the peeled row, the partial
   auto tail = [&](int f, const Epi& C) {
     if constexpr (PROJ) {
