@@ -387,7 +387,8 @@ __device__ __forceinline__ void mixed_channels(const DevModel& m, const RowsWork
   // Row tile tt: its products with chunks K0 and up (tile tt > 0 of the projected
   // form has none with the chunks before), and the residuals of its first QN
   // groups of eight rows (a later group holds padding only, whose sums and
-  // targets are zero).  QN = 0: `jq` groups (direct form: rows past T masked).
+  // targets are zero).  QN = 0: `jq` groups (direct form: rows past T masked).  QN =
+  // -1: all four, in the last tile with rows past T masked (WHOLE).
   //
   // MF(acc, q, p): the product of matrix digit q and power digit p.  The even levels
   // (0, 2 and 4) depend on no shift; the odd ones (1, 3 and 5) come after the
