@@ -1138,24 +1138,24 @@ __attribute__((amdgpu_waves_per_eu(grad_waves<NQB, AB>()))) void k_grad64(
   // operands need the longer rows only.)
   const int swz = PROJ ? (lane >> 4) & 2 : 0, tswz = PROJ ? lane & 2 : 0;
   const int pieces = TR * 4 * (int)sizeof(AT);       // of 16 bytes in a quad row
-  const int psh = pieces <= 16 ? 4 : pieces <= 32 ? 5 : 6;   // log2 of the lanes a row takes
+  const int kp = ks * (int)sizeof(AT) / 16, kds = NQB * TR * 64;
+  const unsigned inv = (unsigned)(0xffffffffu / (unsigned)pieces) + 1;   // e / pieces = umulhi(e, inv), pieces >= 16
   const int c0 = ch * per, c1 = min(m.F, c0 + per);
   for (int cs = c0; cs < c1; cs += fs) {
     const int fn = min(fs, c1 - cs);
     __syncthreads();                        // the previous stage is consumed
-    // the staged quad rows (all tiles of one region quad) over the wave's lanes, 16
-    // or 32 lanes to a row where it has no more pieces (16-row tiles: 16 pieces in
-    // FP32 and 32 in FP64 each); in FP64 the regions 2 and 3 of a quad exchange
-    // pairs of matrix rows on the way, see `swz`.  (A wave a row left most lanes
-    // idle in short rows, call us: 40 regions, 301 channels, 16 bins, 4096 rows 165,
-    // now 148; 48, 154, 2, 16384 rows 316, 286; 15, 151, 60 bins projected, 16384
-    // rows 105, 101.  Before the longer rows, with one flat copy, 170, 315 and 122.)
-    for (int row = (wave * 64 + lane) >> psh; row < fn * NQB; row += (W * 64) >> psh) {
-      const uint4* src = reinterpret_cast<const uint4*>(kg + ((size_t)cs * NQB + row) * TR * 64);
-      uint4* dst = reinterpret_cast<uint4*>(s_k + (size_t)row * ks);
-      for (int k = lane & ((1 << psh) - 1); k < pieces; k += 1 << psh) {
-        dst[PROJ ? k ^ ((k >> 4) & 1) : k] = src[k];
-      }
+    // the staged quad rows (all tiles of one region quad), one flat copy over all
+    // threads: piece k of row goes to the row's padded place; in FP64 the regions 2
+    // and 3 of a quad exchange pairs of matrix rows on the way, see `swz`.  (A wave
+    // a row left lanes idle in a row's last pass, and 48 of 64 in rows of 16 pieces;
+    // call us: 32 regions, 301 channels, 96 bins, 8192 rows 256, now 238; 40, 301, 16,
+    // 4096 167, 148; 48, 154, 2, 16384 313, 282; 15, 151, 60 projected, 16384 108,
+    // 103; 2 x 16 masks, 301, 96, 4096 200, 179.)
+    const uint4* src = reinterpret_cast<const uint4*>(kg + (size_t)cs * kds);
+    uint4* dst = reinterpret_cast<uint4*>(s_k);
+    for (int e = threadIdx.x; e < fn * NQB * pieces; e += W * 64) {
+      const int row = __umulhi((unsigned)e, inv), k = e - row * pieces;
+      dst[row * kp + (PROJ ? k ^ ((k >> 4) & 1) : k)] = src[e];
     }
     stage(s_D, dg + (size_t)cs * drow, fn * drow * 8);
     __syncthreads();
